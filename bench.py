@@ -108,6 +108,24 @@ def executed_int8_ops_per_gate(p):
     return sum(n * (2 * min(k + 1, i + 2) * ell + 2 * ell) for i in range(k)) * 8 * N * N
 
 
+PEAK_FP64_VECTOR = 256 * 64 * 2 * 2.4e9   # one 64-lane FMA per compute unit and cycle
+
+
+def executed_fp64_flops_per_gate(p):
+    """Double precision operations the transform-domain rotation executes per
+    gate.  A 512-point transform has 9 x 256 butterflies: 6 fused
+    multiply-adds each forward; inverse 4 additions and 2 fused multiply-adds
+    each and, but for the last two levels, 2 multiplications.  Every result
+    transforms back twice (two 16-bit halves of the key), every product of
+    transforms is 4 fused multiply-adds per point and half.  A step of party
+    i has L = min(k+1, i+2) live slots: (L + 1) ell forward and 2 (L + 1)
+    inverse transforms, (2 L + 2) ell products."""
+    k, n, ell, h = p["k"], p["n"], p["bk_ell"], p["N"] // 2
+    fwd, inv = 9 * 256 * 12, 9 * 256 * 8 + 7 * 256 * 2
+    return sum(n * ((L + 1) * ell * fwd + 2 * (L + 1) * inv + (2 * L + 2) * ell * 2 * 8 * h)
+               for L in (min(k + 1, i + 2) for i in range(k)))
+
+
 # ------------------------------------------------------- CPU baseline ----
 _CPU = {}
 
@@ -624,11 +642,24 @@ def main():
     _, ms, ln = timed(head, 1, 0, level=2)
     br_ms = ms[1] / max(ln[1], 1)
     macs = macs_per_gate(C2) * BATCH
-    persistent = head == mk.PATH_MFMA_I8 and ln[4] > 0 and ln[5] == 0
+    one_launch = head == mk.PATH_MFMA_I8 and ln[4] > 0 and ln[5] == 0
+    persistent = one_launch and ctx.get_team_rows(BATCH) > 0
+    transform = one_launch and not persistent
     # extraction and key switching inside the persistent launch: no
     # separate key-switching stage was timed
     ks_fused = persistent and ln[2] == 0
-    if persistent:
+    if transform:
+        # dominant kernel: the transform-domain rotation (all 1120 CMux steps
+        # of every gate in one launch), double precision on the vector units
+        flops = executed_fp64_flops_per_gate(C2) * BATCH
+        kms = ms[4] / ln[4]
+        achieved = flops / (kms * 1e-3)
+        roof = {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_FP64_VECTOR / 1e12,
+                "unit": "TFLOP/s fp64", "frac": achieved / PEAK_FP64_VECTOR, "traffic": None,
+                "kernel": "fft_lean_kernel", "avg_launch_ms": kms, "launches": ln[4],
+                "fp64_flops_per_launch": flops,
+                "full_hybrid_product_tops": 8 * macs / (kms * 1e-3) / 1e12}
+    elif persistent:
         # dominant kernel: the persistent rotation (all 1120 CMux steps of
         # the batch in one launch); executed int8 ops with live-slot
         # skipping.  With key switching fused the launch also switches the
@@ -677,7 +708,7 @@ def main():
         "value": value, "unit": "gates/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": sec * 1e3, "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None,
-        "dtype": "int8" if head == mk.PATH_MFMA_I8 else "int32", "data": "synthetic",
+        "dtype": "fp64" if transform else "int8" if head == mk.PATH_MFMA_I8 else "int32", "data": "synthetic",
         "config": {"workload": "1024 mixed bootstrapped MK gates (AND/OR/NOR/XOR/XNOR/NAND), "
                                "k=2 n=560 N=1024 B=2^8 ell=3 B'=2^2 t=8",
                    "global_batch": BATCH, "path": args.path, "parallelism": "single GPU"},
@@ -688,11 +719,12 @@ def main():
         # rotation kernel as well
         "stage_ms_per_step": {"precombine": hms[0] / args.steps, "blind_rotate": hms[1] / args.steps,
                               "extract_keyswitch": hms[2] / args.steps},
-        "kernel_ms_instrumented_step": ({"persistent_rotation": ms[4], "blind_rotate_stage": ms[1]}
-                                        if persistent else
+        "kernel_ms_instrumented_step": ({"persistent_rotation" if persistent else "transform_rotation": ms[4],
+                                         "blind_rotate_stage": ms[1]}
+                                        if one_launch else
                                         {"mfma_gemm1": ms[4], "mfma_gemm2": ms[5], "rotdec": ms[6],
                                          "wdec": ms[7], "blind_rotate_stage": ms[1]}),
-        "rotation_schedule": "persistent" if persistent else "stream-ordered",
+        "rotation_schedule": "persistent" if persistent else "transform" if transform else "stream-ordered",
         "key_switch_fused": ks_fused,
         "roofline": roof,
         "cpu_baseline": cpu,

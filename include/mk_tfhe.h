@@ -63,7 +63,8 @@ extern "C" {
 
 /* Blind-rotation implementations (bit-identical results). */
 #define MK_PATH_I32 0     /* exact 32-bit integer VALU products            */
-#define MK_PATH_MFMA_I8 1 /* exact split-limb int8 MFMA products           */
+#define MK_PATH_MFMA_I8 1 /* fast path: split-limb int8 MFMA products, or
+                             exact transforms (mk_set_rotation)            */
 
 /* ------------------------------------------------------- parameters ---- */
 /*
@@ -225,7 +226,8 @@ int mk_eval_circuit(mk_ctx *ctx, const mk_circuit *c, const uint32_t *in_dev,
  * captures, on a stream of its own, the evaluation reading in_dev and
  * writing out_dev (layouts as in mk_eval_circuit); in_dev and out_dev must
  * stay valid for the graph's lifetime.  The capture is cut into consecutive
- * pieces of about 1024 kernels (256 CMux steps), since a single graph of a
+ * pieces of about 1024 kernels (256 CMux steps; a transform-domain rotation is
+ * cut after as many steps), since a single graph of a
  * whole operator (thousands of kernels per level) is beyond what graph
  * instantiation handles.  Each mk_graph_launch on `stream` replays the
  * pieces in order and so evaluates the circuit on the current contents of
@@ -346,7 +348,8 @@ int mk_build_naive_gate(int type, mk_gate *gates, int32_t *n_gates, int32_t *n_w
  * for the events and returns accumulated milliseconds and launch counts for
  * MK_PROFILE_SLOTS slots: [0] pre-combination, [1] blind rotation (whole),
  * [2] extraction + key switching, [3] circuit bookkeeping, [4] MFMA stage-1
- * GEMM or the persistent rotation kernel, [5] MFMA stage-2 GEMM, [6] rotate
+ * GEMM, or the persistent or transform-domain rotation kernel, [5] MFMA
+ * stage-2 GEMM, [6] rotate
  * + decompose, [7] w decompose.
  * reset != 0 clears the accumulators.  Errors: MK_EINVAL. */
 #define MK_PROFILE_SLOTS 8
@@ -394,8 +397,8 @@ int mk_get_split(const mk_ctx *ctx, size_t count, int32_t *parts);
 int mk_get_tiles(const mk_ctx *ctx, size_t count, int32_t *gemm1_shape,
                  int32_t *gemm2_shape);
 
-/* Schedule of the int8-MFMA blind rotation (§3.1: a level's gates are
- * independent, so all of them run together).  Both schedules give
+/* Schedule of the blind rotation on MK_PATH_MFMA_I8 (§3.1: a level's gates
+ * are independent, so all of them run together).  Every schedule gives
  * bit-identical results.
  *   MK_ROT_STREAM      every CMux step is four stream-ordered kernels
  *                      (rotate + decompose, stage-1 GEMM, w decompose,
@@ -405,11 +408,15 @@ int mk_get_tiles(const mk_ctx *ctx, size_t count, int32_t *gemm1_shape,
  *                      workgroups runs it, meeting at a barrier after each
  *                      phase of a CMux step (rotate + decompose, stage 1,
  *                      stage 2).  Needs N in {128, 256, 512, 1024, 2048}.
- *   MK_ROT_AUTO        the persistent schedule where it is faster: at
- *                      N = 1024 for batches of at least one tile per XCD
- *                      (256 gates on MI355X), with teams sized to the batch
- *                      (mk_set_team_rows), at other N from 2.5 tiles per
- *                      XCD; stream-ordered kernels below (default).
+ *   MK_ROT_AUTO        (default) at N = 1024 the transform-domain rotation:
+ *                      each gate's CMux steps in one workgroup, the products
+ *                      through double precision transforms whose results are
+ *                      proved to round to the exact integers.  With tile
+ *                      shapes or a team size forced (mk_set_tiles,
+ *                      mk_set_team_rows) the int8 kernels: persistent from
+ *                      one tile per XCD on (256 gates on MI355X), stream-
+ *                      ordered below.  At other N the persistent schedule
+ *                      from 2.5 tiles per XCD on, stream-ordered below.
  * Errors: MK_EINVAL. */
 #define MK_ROT_AUTO -1
 #define MK_ROT_STREAM 0
@@ -432,7 +439,7 @@ int mk_set_ks_fusion(mk_ctx *ctx, int on);
  * three on.  rows = 2, 4 or 8 forces that size (tuning and tests).  Every
  * size gives the same words.  mk_get_team_rows reports the size a rotation
  * of `count` gates runs with (also at other N, where it is fixed), or 0 when
- * it runs on the stream-ordered kernels (always before mk_upload_eval_key,
+ * it does not run on the persistent schedule (always before mk_upload_eval_key,
  * which finds the XCDs).
  * Errors: MK_EINVAL (other values, or rows != 0 at N != 1024). */
 int mk_set_team_rows(mk_ctx *ctx, int rows);

@@ -5,12 +5,13 @@
 //                      Z_2N (§4.1 Eqs. (6)-(11), Algs. 1-2)
 //   K2 br_plain        blind rotation, exact 32-bit integer VALU products
 //   K3 br_mfma         blind rotation, exact split-limb int8 MFMA products
-//                      (mk_mfma.hip)
+//                      (mk_mfma.hip), or the same integers through double
+//                      precision transforms (mk_fft.hip)
 //   K4 extract_ks      sample extraction, + 1/8, multi-key key switching
 //                      (§3.2 MKKeySwitch)
 //
-// All arithmetic is on Torus32 words and wraps mod 2^32; nothing on the GPU
-// uses floating point.
+// All arithmetic is on Torus32 words and wraps mod 2^32; floating point is used
+// only inside the transforms, whose results are rounded to exact integers.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -100,7 +101,7 @@ void device_release(mk_ctx *ctx) {
     drain_events(ctx);
     DeviceKeys &D = ctx->dev;
     void *ptrs[] = {D.bk_ext, D.evk_ext, D.bk_win, D.evk_win, D.ks, D.ks_win, D.scratch, D.mfma_scratch,
-                    D.ks_scratch, D.circ_scratch, D.status};
+                    D.ks_scratch, D.circ_scratch, D.status, D.fft_bk, D.fft_evk, D.fft_tab};
     bool any = false;
     for (void *p : ptrs) any |= p != nullptr;
     if (any) {
@@ -177,6 +178,7 @@ int device_upload(mk_ctx *ctx, void *stream) {
     if ((rc = dev_alloc_copy(&D.ks, ks, s, "ks"))) return rc;
     if ((rc = mfma_upload(ctx, evk, s))) return rc;
     if ((rc = ks_mfma_upload(ctx, s))) return rc;
+    if ((rc = fft_upload(ctx, s))) return rc;
     MK_HIP(hipStreamSynchronize(s), "upload sync");
     D.uploaded = true;
     return MK_OK;

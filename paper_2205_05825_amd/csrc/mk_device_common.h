@@ -53,6 +53,11 @@ bool use_persist(const mk_ctx *ctx, int GT);
 // Gates of the first of two consecutive rotation launches for a batch of
 // `count` (count itself when one launch is best).
 size_t mfma_rotation_split(const mk_ctx *ctx, size_t count);
+// Transform-domain rotation (mk_fft.hip): whether rotations run on it, and
+// CMux steps 0 .. steps-1 of `count` gates into acc rows of (k+1) N words.
+int fft_upload(mk_ctx *ctx, hipStream_t s);
+bool use_fft(const mk_ctx *ctx);
+int launch_br_fft(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc, size_t count, int steps, hipStream_t s);
 // Persistent rotation (mk_persist.hip).
 struct MfmaArgs;
 struct KsFused;
@@ -72,6 +77,8 @@ int ks_fused_args(mk_ctx *ctx, size_t count, uint32_t *out, size_t stride, hipSt
 // During a graph capture: ends the current graph after enough kernels and
 // begins the next one on the same stream (mk_engine.hip).
 int capture_checkpoint(mk_ctx *ctx, hipStream_t s, int kernels);
+// Kernels left in the current graph piece (INT_MAX outside a capture).
+int capture_room(const mk_ctx *ctx);
 // The whole gate pipeline on `count` gates (mk_device.hip).
 int run_gates(mk_ctx *ctx, const uint8_t *types, const uint32_t *in1, const uint32_t *in2,
               uint32_t *out, size_t count, size_t stride, int path, hipStream_t s);

@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <list>
 #include <new>
 #include <string>
@@ -490,6 +491,11 @@ int capture_checkpoint(mk_ctx *ctx, hipStream_t s, int kernels) {
     if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) != hipSuccess)
         return fail(MK_EDEVICE, "graph capture: starting a piece failed");
     return MK_OK;
+}
+
+int capture_room(const mk_ctx *ctx) {
+    const CaptureState *cs = (const CaptureState *)ctx->dev.capture;
+    return cs ? std::max(1, cs->piece - cs->kernels) : INT_MAX;
 }
 
 void graph_release(mk_graph *g) {

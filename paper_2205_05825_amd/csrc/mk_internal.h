@@ -38,6 +38,8 @@ struct DeviceKeys {
     int8_t *bk_win = nullptr;
     int8_t *evk_win = nullptr;
     size_t bk_win_bytes = 0, evk_win_bytes = 0;
+    // Transform-domain path (mk_fft.hip): transformed keys and twiddles.
+    void *fft_bk = nullptr, *fft_evk = nullptr, *fft_tab = nullptr;
     uint32_t *ks = nullptr;       // [k][N][t][B'-1][n+1]
     int8_t *ks_win = nullptr;     // MFMA key-switching tiles (mk_keyswitch.hip)
     size_t ks_win_bytes = 0;

@@ -595,8 +595,9 @@ static uint32_t *ctl_of(const MfmaArgs &a) {
     return (uint32_t *)(a.V + (size_t)a.ell * a.GP * a.N);
 }
 
-// Whether the persistent rotation runs a batch of GT gate tiles: by choice
-// (mk_set_rotation), else at N = 1024 from one tile per XCD on (the team
+// Whether the persistent rotation runs a batch of GT gate tiles: not where the
+// automatic choice is the transform-domain rotation (use_fft), by choice
+// (mk_set_rotation), else (with forced team sizes or tiles) at N = 1024 from one tile per XCD on (the team
 // size then follows the batch width, persist_team_rows), and at other N from
 // 2.5 tiles per XCD on.  Measured on MI355X at the Table 7 shape, stream-
 // ordered against persistent (ms per batch, team size in brackets): 128
@@ -607,6 +608,7 @@ static uint32_t *ctl_of(const MfmaArgs &a) {
 // many compute units.
 bool use_persist(const mk_ctx *ctx, int GT) {
     const DeviceKeys &D = ctx->dev;
+    if (use_fft(ctx)) return false;
     if (D.rot_kind == MK_ROT_STREAM || D.num_xcd <= 0 || !persist_supported(ctx->p)) return false;
     if (D.rot_kind == MK_ROT_PERSISTENT) return true;
     return ctx->p.N == 1024 ? GT >= D.num_xcd : 2 * GT >= 5 * D.num_xcd;
@@ -817,6 +819,14 @@ static int join_parts(mk_ctx *ctx, int parts, hipStream_t s, hipStream_t *ss) {
 int launch_br_mfma(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc_out, size_t count, int steps,
                    hipStream_t s, uint32_t *ks_out, size_t ks_stride, bool *ks_done) {
     const mk_params &P = ctx->p;
+    if (use_fft(ctx)) {
+        // one gate needs no scratch of its own; the batch limit is the same as
+        // the int8 kernels'
+        const size_t GP = (count + 31) / 32 * 32;
+        if ((size_t)(P.k + 1) * P.bk_ell * GP * P.N >= ((size_t)1 << 31))
+            return fail(MK_EINVAL, "int8-MFMA path: batch too large for one launch (split it)");
+        return launch_br_fft(ctx, abar, acc_out, count, steps, s);
+    }
     Split sp = split_for(ctx, count);
     // per-kernel timing and graph capture see a single stream
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;

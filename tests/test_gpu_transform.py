@@ -1,0 +1,116 @@
+"""The transform-domain blind rotation (the automatic schedule at N = 1024)
+against the stream-ordered int8 kernels and the oracle, word for word (needs
+an MI355X).  Short LWE dimensions keep the key small; the ring is the Table 7
+one, the only one this schedule runs."""
+import struct
+
+import numpy as np
+import pytest
+
+from oracle import params as OP
+from oracle import tfhe
+from tests import helpers
+
+pytestmark = pytest.mark.gpu
+
+AUTO, STREAM = -1, 0
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    return torch
+
+
+def _params(k, n, ell):
+    return OP.Params(k=k, n=n, N=1024, bk_ell=ell, ks_t=8, bk_noise_log2=30, ks_noise_log2=15, lwe_noise_log2=15)
+
+
+def _world(P, seed):
+    import paper_2205_05825_amd as mk
+    ctx = mk.Context(helpers.lib_params(P), seed)
+    for i in range(P.k):
+        ctx.keygen(i, tfhe.party_seed(seed, i))
+    return ctx
+
+
+def _rotate(torch, ctx, abar, steps, kind):
+    P = ctx.params
+    ta = torch.from_numpy(np.ascontiguousarray(abar).view(np.int32)).to("cuda:0")
+    acc = torch.full((len(abar), (P.k + 1) * P.N), 5, dtype=torch.int32, device="cuda:0")
+    ctx.set_rotation(kind)
+    try:
+        ctx.blind_rotate(ta, acc, max_steps=steps)
+    finally:
+        ctx.set_rotation(AUTO)
+    torch.cuda.synchronize()
+    return acc.cpu().numpy().view(np.uint32)
+
+
+def _abar(P, cnt, seed):
+    a = np.random.default_rng(seed).integers(0, 2 * P.N, (cnt, P.lwe_words)).astype(np.uint32)
+    a[0, :] = 0                      # every step adds zero
+    a[-1, :] = 2 * P.N - 1
+    a[cnt // 2, 1::2] = 0
+    a[cnt // 3, :] = P.N
+    return a
+
+
+@pytest.mark.parametrize("k,ell", [(1, 3), (2, 3), (2, 1), (2, 2), (3, 3), (4, 3), (5, 2), (8, 3)])
+def test_party_counts_and_gadget_lengths(torch_cuda, k, ell):
+    """Every accumulator word equals the stream-ordered schedule's for one
+    gate and for counts on both sides of the one-gate-per-compute-unit limit
+    (up to 2 rounds of 256 at k <= 2), across every party boundary, and the
+    oracle's on a few gates."""
+    P = _params(k, 5, ell)
+    ctx = _world(P, 40 + k)
+    ctx.upload()
+    K = tfhe.generate(P, 40 + k)
+    for cnt in (1, 3, 257, 514):
+        abar = _abar(P, cnt, 10 * k + cnt)
+        got = _rotate(torch_cuda, ctx, abar, -1, AUTO)
+        assert np.array_equal(got, _rotate(torch_cuda, ctx, abar, -1, STREAM)), cnt
+        if cnt == 3:
+            for g in range(cnt):
+                assert np.array_equal(got[g].reshape(k + 1, P.N), tfhe.blind_rotate(K, abar[g].astype(np.int64))), g
+    ctx.close()
+
+
+@pytest.mark.parametrize("steps", [0, 1, 4, 7])
+def test_partial_rotations(torch_cuda, steps):
+    """max_steps from none to across the party boundary, both kernels."""
+    P = _params(2, 6, 3)
+    ctx = _world(P, 50)
+    ctx.upload()
+    for cnt in (2, 600):
+        abar = _abar(P, cnt, steps + cnt)
+        assert np.array_equal(_rotate(torch_cuda, ctx, abar, steps, AUTO),
+                              _rotate(torch_cuda, ctx, abar, steps, STREAM)), cnt
+    ctx.close()
+
+
+@pytest.mark.parametrize("k,pattern", [(2, "min"), (2, "max"), (2, "halves"), (2, "alternate"), (8, "halves")])
+def test_extreme_keys(torch_cuda, k, pattern):
+    """Imported key polynomials at the ends of both 16-bit halves, constant
+    (every product concentrated on one result and frequency) or alternating:
+    the largest sums the rounding has to get right.  Every word equals the
+    exact int8 schedule's."""
+    P = _params(k, 4, 3)
+    ctx = _world(P, 60)
+    words = {"min": [0x80000000], "max": [0x7FFF7FFF], "halves": [0x80008000],
+             "alternate": [0x7FFF7FFF, 0x80008000]}[pattern]
+    head = 4 + 4 + 40 + 4
+    for party in range(k):
+        data = bytearray(ctx.export_keys(party))
+        assert struct.unpack_from("<4s", data)[0] == b"MKK1"
+        pk = head + P.n + P.N
+        polys = 3 + P.n * 9
+        fill = np.tile(np.array(words, np.uint32), polys * P.N // len(words))
+        data[pk:pk + 4 * polys * P.N] = fill.tobytes()
+        ctx.import_keys(party, bytes(data))
+    ctx.upload()
+    for cnt in (2, 520):
+        abar = _abar(P, cnt, cnt)
+        assert np.array_equal(_rotate(torch_cuda, ctx, abar, -1, AUTO), _rotate(torch_cuda, ctx, abar, -1, STREAM)), cnt
+    ctx.close()
