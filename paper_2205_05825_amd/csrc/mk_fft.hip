@@ -190,11 +190,25 @@ __device__ __forceinline__ void lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-__device__ __forceinline__ Cx ld(const d2 *p) {
-    const d2 v = *p;
+// LDS is addressed by byte offsets from the start of the workgroup's block, so
+// that a word's exclusive-or pattern is one instruction away from its address.
+extern __shared__ __align__(16) unsigned char smem[];
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+typedef __attribute__((address_space(3))) d2 lds_d2;
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+__device__ __forceinline__ lds_byte *lds_at(uint32_t off) { return (lds_byte *)smem + off; }
+__device__ __forceinline__ Cx ld(uint32_t off) {
+    const d2 v = *(lds_d2 *)lds_at(off);
     return {v.x, v.y};
 }
-__device__ __forceinline__ void st(d2 *p, const Cx &v) { *p = d2{v.r, v.i}; }
+__device__ __forceinline__ void st(uint32_t off, const Cx &v) { *(lds_d2 *)lds_at(off) = d2{v.r, v.i}; }
+__device__ __forceinline__ uint32_t ldw(uint32_t off) { return *(lds_u32 *)lds_at(off); }
+__device__ __forceinline__ void stw(uint32_t off, uint32_t v) { *(lds_u32 *)lds_at(off) = v; }
+__device__ __forceinline__ void addw(uint32_t off, uint32_t v) {
+    __hip_atomic_fetch_add((lds_u32 *)lds_at(off), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+constexpr uint32_t kBufBytes = kH * 16;   // one transform
+constexpr uint32_t kRowBytes = kN * 4;    // one polynomial
 
 // Exchanges the register pair's bit with lane bit 5 (W = 32) or 4 (W = 16).
 template <int W>
@@ -224,23 +238,34 @@ __device__ __forceinline__ void swap_bit(Cx &a, Cx &b) {
     swap_bit<W>(a.i, b.i);
 }
 
-// Lane layouts and LDS words of point j = (j8 .. j0) of a transform.
+// LDS bytes of point j = (j8 .. j0) of a transform for this lane's two
+// layouts.  Packed, so that they can stay in two registers.
 struct Lane {
-    int e0, e1;   // exchange words of the outer layout, j6 = 0 and 1 (j5 = j4 = 0)
-    int e, h;     // exchange and hand-over words of the inner layout, j3 = j2 = j1 = 0
+    uint32_t e, h;   // exchange (outer | inner << 16) and hand-over (inner)
     __device__ __forceinline__ explicit Lane(int l) {
-        {   // outer: lane (j8 j7 j3 j2 j1 j0), registers (j5 j4 j6)
-            const int j8 = l >> 5, j7 = (l >> 4) & 1;
-            e0 = (l >> 4) * 128 + ((l & 15) ^ ((j8 ^ j7) << 3) ^ (j7 << 2));
-            e1 = 64 + (e0 ^ 2);
-        }
-        {   // inner: lane (j4 j5 j8 j7 j6 j0), registers (j3 j2 j1)
-            const int j0 = l & 1, j6 = (l >> 1) & 1, j7 = (l >> 2) & 1, j8 = (l >> 3) & 1, j5 = (l >> 4) & 1, j4 = l >> 5;
-            const int b5 = j8 * 16 + j7 * 8 + j6 * 4 + j5 * 2 + j4;
-            e = b5 * 16 + (j0 ^ ((j8 ^ j7) << 3) ^ (j7 << 2) ^ (j6 << 1));
-            h = j0 * 256 + (b5 >> 1) * 16 + ((j4 ^ j8) << 3) + (j7 * 4 + j6 * 2 + j0);
-        }
+        // outer: lane (j8 j7 j3 j2 j1 j0), registers (j5 j4 j6)
+        const int o8 = l >> 5, o7 = (l >> 4) & 1;
+        const int outer = (l >> 4) * 128 + ((l & 15) ^ ((o8 ^ o7) << 3) ^ (o7 << 2));
+        // inner: lane (j4 j5 j8 j7 j6 j0), registers (j3 j2 j1)
+        const int j0 = l & 1, j6 = (l >> 1) & 1, j7 = (l >> 2) & 1, j8 = (l >> 3) & 1, j5 = (l >> 4) & 1, j4 = l >> 5;
+        const int b5 = j8 * 16 + j7 * 8 + j6 * 4 + j5 * 2 + j4;
+        const int inner = b5 * 16 + (j0 ^ ((j8 ^ j7) << 3) ^ (j7 << 2) ^ (j6 << 1));
+        e = (uint32_t)outer * 16 | (uint32_t)inner << 20;
+        h = (uint32_t)(j0 * 256 + (b5 >> 1) * 16 + ((j4 ^ j8) << 3) + (j7 * 4 + j6 * 2 + j0)) * 16;
     }
+    __device__ __forceinline__ Lane here() const {   // see here(int)
+        Lane v = *this;
+        asm volatile("" : "+v"(v.e), "+v"(v.h));
+        return v;
+    }
+    // register r of the outer layout, of the inner one, and its hand-over word,
+    // in the buffer at `buf` (a multiple of 4 KB)
+    __device__ __forceinline__ uint32_t outer(uint32_t buf, int r) const {
+        const uint32_t b = buf + (e & 0xFFFFu);
+        return ((r & 1) ? (b ^ 32u) + 1024u : b) + (uint32_t)((r >> 2) * 512 + ((r >> 1) & 1) * 256);
+    }
+    __device__ __forceinline__ uint32_t inner(uint32_t buf, int r) const { return (buf + (e >> 16)) ^ (uint32_t)(32 * r); }
+    __device__ __forceinline__ uint32_t hand(uint32_t buf, int r) const { return (buf + h) ^ (uint32_t)(16 * r); }
 };
 // Hand-over word of thread c = (j8 .. j1), j0 = 0 (j0 = 1: 256 + (word ^ 1))
 __device__ __forceinline__ int owner_word(int c) {
@@ -249,8 +274,7 @@ __device__ __forceinline__ int owner_word(int c) {
 
 // Levels 1 .. 8 of a transform by one wave.  x[r]: point 64 r + lane; the
 // result goes to `buf` in hand-over order.
-__device__ __forceinline__ void fwd_levels(Cx (&x)[8], int l, d2 *buf, const d2 *tab) {
-    const Lane at(l);
+__device__ __forceinline__ void fwd_levels(Cx (&x)[8], int l, const Lane &at, uint32_t buf, const d2 *tab) {
     d2 tp[4], tq[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) tp[i] = tab[kTabP + (l >> 4) * 4 + i];
@@ -275,24 +299,26 @@ __device__ __forceinline__ void fwd_levels(Cx (&x)[8], int l, d2 *buf, const d2 
         bf_fwd<true>(x[j6 + 4], x[j6 + 6], tp[2 + j6].x, tp[2 + j6].y);
     }
 #pragma unroll
-    for (int r = 0; r < 8; ++r) st(buf + ((r & 1) ? at.e1 : at.e0) + (r >> 2) * 32 + ((r >> 1) & 1) * 16, x[r]);
+    for (int r = 0; r < 8; ++r) st(at.outer(buf, r), x[r]);
     wave_fence();
 #pragma unroll
-    for (int r = 0; r < 8; ++r) x[r] = ld(buf + (at.e ^ (2 * r)));
+    for (int r = 0; r < 8; ++r) x[r] = ld(at.inner(buf, r));
     radix8_fwd(x, [&](int i) { return Tw{tq[i].x, tq[i].y}; });
     wave_fence();
 #pragma unroll
-    for (int r = 0; r < 8; ++r) st(buf + (at.h ^ r), x[r]);
+    for (int r = 0; r < 8; ++r) st(at.hand(buf, r), x[r]);
 }
 
 // Digit (24 - sh) / 8 of the coefficients y, FLIP: y still has its bias.
 template <bool FLIP>
-__device__ __forceinline__ void wave_fwd(const uint32_t *y, int sh, int lane, d2 *buf, const d2 *tab) {
+__device__ __forceinline__ void wave_fwd(uint32_t y, int sh, int lane, const Lane &lane_at, uint32_t buf, const d2 *tab) {
     const int l = here(lane);
+    const Lane at = lane_at.here();
+    const uint32_t yl = y + 4u * (uint32_t)l;
     Cx x[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
-        uint32_t a = y[l + 64 * r], b = y[l + 64 * r + kH];
+        uint32_t a = ldw(yl + 256u * r), b = ldw(yl + 256u * r + kRowBytes / 2);
         if constexpr (FLIP) {
             a ^= 0x80808080u;
             b ^= 0x80808080u;
@@ -300,7 +326,7 @@ __device__ __forceinline__ void wave_fwd(const uint32_t *y, int sh, int lane, d2
         x[r].r = (double)(int)__builtin_amdgcn_sbfe(a, sh, 8);
         x[r].i = (double)(int)__builtin_amdgcn_sbfe(b, sh, 8);
     }
-    fwd_levels(x, l, buf, tab);
+    fwd_levels(x, l, at, buf, tab);
 }
 
 __device__ __forceinline__ uint32_t round_word(double x, double s) {
@@ -310,24 +336,25 @@ __device__ __forceinline__ uint32_t round_word(double x, double s) {
 
 // Levels 8 .. 1 of an inverse transform by one wave, from hand-over order;
 // every coefficient, rounded and shifted left by `sh`, is added to dst.
-__device__ __forceinline__ void wave_inv(d2 *buf, uint32_t *dst, int sh, int lane, const d2 *tab) {
+__device__ __forceinline__ void wave_inv(uint32_t buf, uint32_t dst, int sh, int lane, const Lane &lane_at, const d2 *tab) {
     const int l = here(lane);
-    const Lane at(l);
+    const Lane at = lane_at.here();
+    const uint32_t dl = dst + 4u * (uint32_t)l;
     d2 tp[4], tq[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) tq[i] = tab[kTabQ + 64 * i + l];
     Cx x[8];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) x[r] = ld(buf + (at.h ^ r));
+    for (int r = 0; r < 8; ++r) x[r] = ld(at.hand(buf, r));
 #pragma unroll
     for (int i = 0; i < 4; ++i) tp[i] = tab[kTabP + (l >> 4) * 4 + i];
     radix8_inv<false>(x, [&](int i) { return Tw{tq[i].x, tq[i].y}; });
     wave_fence();
 #pragma unroll
-    for (int r = 0; r < 8; ++r) st(buf + (at.e ^ (2 * r)), x[r]);
+    for (int r = 0; r < 8; ++r) st(at.inner(buf, r), x[r]);
     wave_fence();
 #pragma unroll
-    for (int r = 0; r < 8; ++r) x[r] = ld(buf + ((r & 1) ? at.e1 : at.e0) + (r >> 2) * 32 + ((r >> 1) & 1) * 16);
+    for (int r = 0; r < 8; ++r) x[r] = ld(at.outer(buf, r));
 #pragma unroll
     for (int j6 = 0; j6 < 2; ++j6) {   // level 5
         bf_inv<false, true>(x[j6], x[j6 + 2], tp[2 + j6].x, tp[2 + j6].y);
@@ -349,8 +376,8 @@ __device__ __forceinline__ void wave_inv(d2 *buf, uint32_t *dst, int sh, int lan
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
         const double s = (1.0 / kH) * ((r & 2) ? kTwA[1].c : 1.0) * ((r & 4) ? kTwA[0].c : 1.0);
-        atomicAdd(dst + l + 64 * r, round_word(x[r].r, s) << sh);
-        atomicAdd(dst + l + 64 * r + kH, round_word(x[r].i, s) << sh);
+        addw(dl + 256u * r, round_word(x[r].r, s) << sh);
+        addw(dl + 256u * r + kRowBytes / 2, round_word(x[r].i, s) << sh);
     }
 }
 
@@ -377,7 +404,6 @@ struct KeyBlock {
 
 __global__ __launch_bounds__(256) void fft_key_kernel(const uint32_t *__restrict__ ext, const d2 *__restrict__ tab,
                                                       d2 *__restrict__ out) {
-    __shared__ __align__(16) d2 buf[kParts * kH];
     const size_t poly = blockIdx.x;
     const uint32_t *K = ext + poly * 2 * kN + kN;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64);
@@ -391,16 +417,16 @@ __global__ __launch_bounds__(256) void fft_key_kernel(const uint32_t *__restrict
         Cx x[8];
 #pragma unroll
         for (int r = 0; r < 8; ++r) x[r] = {part(l + 64 * r), part(l + 64 * r + kH)};
-        fwd_levels(x, l, buf + wave * kH, tab);
+        fwd_levels(x, l, Lane(l), wave * kBufBytes, tab);
     }
     __syncthreads();
     const d2 t9 = tab[kTab9 + tid];
-    const int at0 = owner_word(tid), at1 = 256 + (at0 ^ 1);
+    const uint32_t at0 = 16u * owner_word(tid), at1 = 4096u + (at0 ^ 16u);
     for (int p = 0; p < kParts; ++p) {
-        Cx a = ld(buf + p * kH + at0), b = ld(buf + p * kH + at1);
+        Cx a = ld(p * kBufBytes + at0), b = ld(p * kBufBytes + at1);
         bf_fwd<false>(a, b, t9.x, t9.y);
-        st(out + poly * kPoly + p * kH + tid, a);
-        st(out + poly * kPoly + p * kH + 256 + tid, b);
+        out[poly * kPoly + p * kH + tid] = d2{a.r, a.i};
+        out[poly * kPoly + p * kH + 256 + tid] = d2{b.r, b.i};
     }
 }
 
@@ -418,7 +444,7 @@ struct FftArgs {
 
 // Accumulators of one gate: X^-b v, 0, .. at the start, else the rows saved before.
 template <int T>
-__device__ __forceinline__ void load_acc(const FftArgs &a, int g, const uint32_t *abar, uint32_t *acc) {
+__device__ __forceinline__ void load_acc(const FftArgs &a, int g, const uint32_t *abar, uint32_t acc) {
     const int words = (a.k + 1) * kN;
     for (int idx = threadIdx.x; idx < words; idx += T) {
         uint32_t v = 0;
@@ -429,36 +455,37 @@ __device__ __forceinline__ void load_acc(const FftArgs &a, int g, const uint32_t
             const uint32_t tv = (s & (kN - 1)) < kN / 2 ? 0xE0000000u : 0x20000000u;
             v = (s & kN) ? 0u - tv : tv;
         }
-        acc[idx] = v;
+        stw(acc + 4u * idx, v);
     }
 }
 
 // X^-shift c - c into y, biased for digit extraction.
 template <int T>
-__device__ __forceinline__ void rotate(const uint32_t *c, int shift, uint32_t offset, int tid, uint32_t *y) {
+__device__ __forceinline__ void rotate(uint32_t c, int shift, uint32_t offset, int tid, uint32_t y) {
 #pragma unroll
     for (int i = 0; i < kN / T; ++i) {
         const int m = tid + T * i, s = m + shift;
-        const uint32_t src = c[s & (kN - 1)], rot = (s & kN) ? 0u - src : src;
-        y[m] = (rot - c[m] + offset) ^ 0x80808080u;
+        const uint32_t src = ldw(c + 4u * (uint32_t)(s & (kN - 1))), rot = (s & kN) ? 0u - src : src;
+        stw(y + 4u * m, (rot - ldw(c + 4u * m) + offset) ^ 0x80808080u);
     }
 }
 
 // The thread's two frequencies of the transform in `buf`, and back.
 struct Owner {
-    int at0, at1;
+    uint32_t at0, at1;
     double c, t;
-    __device__ __forceinline__ Owner(int c_, const d2 *tab) : at0(owner_word(c_)), at1(256 + (owner_word(c_) ^ 1)) {
+    __device__ __forceinline__ Owner(int c_, const d2 *tab)
+        : at0(16u * owner_word(c_)), at1(4096u + (16u * owner_word(c_) ^ 16u)) {
         const d2 v = tab[kTab9 + c_];
         c = v.x;
         t = v.y;
     }
-    __device__ __forceinline__ void get(const d2 *buf, Cx &u, Cx &v) const {
+    __device__ __forceinline__ void get(uint32_t buf, Cx &u, Cx &v) const {
         u = ld(buf + at0);
         v = ld(buf + at1);
         bf_fwd<false>(u, v, c, t);
     }
-    __device__ __forceinline__ void put(d2 *buf, const Cx (&s)[2]) const {
+    __device__ __forceinline__ void put(uint32_t buf, const Cx (&s)[2]) const {
         Cx p = s[0], q = s[1];
         bf_inv<false, true>(p, q, c, t);
         st(buf + at0, p);
@@ -469,17 +496,18 @@ struct Owner {
 constexpr int kLeanT = 256;
 constexpr int kLeanBufs = 3;
 
+template <int ELL>
 __global__ __launch_bounds__(kLeanT, 4) void fft_lean_kernel(FftArgs a) {
-    extern __shared__ __align__(16) uint32_t smem[];
-    const int K1 = a.k + 1, ell = a.ell, tid = threadIdx.x;
-    uint32_t *acc = smem;                        // [K1][N]
-    uint32_t *y = acc + K1 * kN;                 // [N]
-    d2 *buf = reinterpret_cast<d2 *>(y + kN);    // [kLeanBufs][H]
+    constexpr int ell = ELL;
+    const int K1 = a.k + 1, tid = threadIdx.x;
+    // LDS: accumulators [K1][N], y [N], transforms [kLeanBufs][H]
+    const uint32_t acc = 0, y = K1 * kRowBytes, buf = y + kRowBytes;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid & 63;
     const int g = blockIdx.x;
     const uint32_t *abar = a.abar + (size_t)g * (a.k * a.n + 1);
     const d2 *tab = a.tab;
     const Owner own(tid, tab);
+    const Lane at(l);
     load_acc<kLeanT>(a, g, abar, acc);
     int shift = a.st0 < a.st1 ? (int)abar[1 + a.st0] : 0;
     int turn = (int)(blockIdx.x >> 3) + (int)(blockIdx.x >> 8);
@@ -488,8 +516,11 @@ __global__ __launch_bounds__(kLeanT, 4) void fft_lean_kernel(FftArgs a) {
         const int party = step / a.n, bit = step - party * a.n;
         const int next_shift = step + 1 < a.st1 ? (int)abar[2 + step] : 0;
         const KeyBlock kd(a.bk + ((size_t)party * a.n + bit) * 3 * ell * kPoly, 3 * ell, tid), ke(a.evk, K1 * ell, tid);
-        auto rot = [&](int j) { rotate<kLeanT>(acc + j * kN, shift, a.offset, here(tid), y); };
+        auto rot = [&](int j) { rotate<kLeanT>(acc + j * kRowBytes, shift, a.offset, here(tid), y); };
+        // products of the ell transforms with two key polynomials each
         auto madd = [&](const KeyBlock &k0, int p0, Cx (&c0)[kParts][2], const KeyBlock &k1, int p1, Cx (&c1)[kParts][2]) {
+            lds_sync();
+#pragma unroll 1
             for (int d = 0; d < ell; ++d) {
                 d2 x0[kParts][2], x1[kParts][2];
 #pragma unroll
@@ -500,7 +531,7 @@ __global__ __launch_bounds__(kLeanT, 4) void fft_lean_kernel(FftArgs a) {
                         x1[p][s] = k1((p1 + d) * kPoly + p * kH + s * 256);
                     }
                 Cx u, v;
-                own.get(buf + d * kH, u, v);
+                own.get(buf + d * kBufBytes, u, v);
 #pragma unroll
                 for (int p = 0; p < kParts; ++p) {
                     mac(c0[p][0], u, x0[p][0]);
@@ -519,65 +550,61 @@ __global__ __launch_bounds__(kLeanT, 4) void fft_lean_kernel(FftArgs a) {
         };
         auto forward = [&](auto flip) {
             const int v = next(ell);
-            if (v < ell) wave_fwd<decltype(flip)::value>(y, 24 - 8 * v, l, buf + v * kH, tab);
+            if (v < ell) wave_fwd<decltype(flip)::value>(y, 24 - 8 * v, l, at, buf + v * kBufBytes, tab);
         };
-        auto inverse = [&](int tasks, uint32_t *dst) {   // low and high part
+        auto inverse = [&](int tasks, uint32_t dst) {   // low and high part
             const int v = next(tasks);
-            if (v < tasks) wave_inv(buf + v * kH, dst, 16 * v, l, tab);
+            if (v < tasks) wave_inv(buf + v * kBufBytes, dst, 16 * v, l, at, tab);
         };
         Cx w[kParts][2] = {};
         rot(party > 0 ? 1 : 0);
         for (int j = 1; j <= party; ++j) {   // slots without a stage-2 part
             lds_sync();
             forward(std::false_type{});
-            lds_sync();
             Cx cT[kParts][2] = {};
             madd(ke, j * ell, w, kd, 0, cT);
             lds_sync();
             own.put(buf, cT[0]);
-            own.put(buf + kH, cT[1]);
+            own.put(buf + kBufBytes, cT[1]);
             rot(j < party ? j + 1 : 0);
             lds_sync();
-            inverse(2, acc + j * kN);
+            inverse(2, acc + j * kRowBytes);
         }
         lds_sync();
         forward(std::false_type{});
-        lds_sync();
         Cx cA[kParts][2] = {}, cB[kParts][2] = {};
         madd(ke, 0, w, kd, 0, cA);
         rot(1 + party);
         lds_sync();
         forward(std::false_type{});
-        lds_sync();
         madd(ke, (1 + party) * ell, w, kd, 0, cB);
-        for (int i = tid; i < kN; i += kLeanT) y[i] = a.offset;
+        for (int i = tid; i < kN; i += kLeanT) stw(y + 4u * i, a.offset);
         lds_sync();
         own.put(buf, w[0]);
-        own.put(buf + kH, w[1]);
+        own.put(buf + kBufBytes, w[1]);
         lds_sync();
         inverse(2, y);
         lds_sync();
         forward(std::true_type{});
-        lds_sync();
         madd(kd, ell, cA, kd, 2 * ell, cB);
         lds_sync();
         own.put(buf, cA[0]);
-        own.put(buf + kH, cA[1]);
-        own.put(buf + 2 * kH, cB[0]);
+        own.put(buf + kBufBytes, cA[1]);
+        own.put(buf + 2 * kBufBytes, cB[0]);
         lds_sync();
         {
             const int v = next(3);
-            if (v < 3) wave_inv(buf + v * kH, acc + (v < 2 ? 0 : 1 + party) * kN, v == 1 ? 16 : 0, l, tab);
+            if (v < 3) wave_inv(buf + v * kBufBytes, acc + (v < 2 ? 0 : 1 + party) * kRowBytes, v == 1 ? 16 : 0, l, at, tab);
         }
         lds_sync();
         own.put(buf, cB[1]);
         lds_sync();
-        if (next(1) == 0) wave_inv(buf, acc + (1 + party) * kN, 16, l, tab);
+        if (next(1) == 0) wave_inv(buf, acc + (1 + party) * kRowBytes, 16, l, at, tab);
         shift = next_shift;
         lds_sync();
     }
     __syncthreads();
-    for (int idx = tid; idx < K1 * kN; idx += kLeanT) a.acc[(size_t)g * K1 * kN + idx] = acc[idx];
+    for (int idx = tid; idx < K1 * kN; idx += kLeanT) a.acc[(size_t)g * K1 * kN + idx] = ldw(acc + 4u * idx);
 }
 
 size_t fft_lean_lds(int k) { return (size_t)(k + 2) * kN * 4 + (size_t)kLeanBufs * kH * 16; }
@@ -589,19 +616,20 @@ constexpr int kSlots = 3;             // slots whose digits are transformed toge
 constexpr int kFwd = kSlots * kEll;   // buffers of digit transforms
 constexpr int kGateBufs = kFwd + 4;   // and of inverse transforms
 
-template <bool MANY>
+template <int ELL, bool MANY>
 __global__ __launch_bounds__(kGateT, 2) void fft_gate_kernel(FftArgs a) {
-    extern __shared__ __align__(16) uint32_t smem[];
-    const int K1 = a.k + 1, ell = a.ell, tid = threadIdx.x;
-    uint32_t *acc = smem;                                // [K1][N]
-    uint32_t *y = acc + K1 * kN;                         // [kSlots][N]
-    d2 *buf = reinterpret_cast<d2 *>(y + kSlots * kN);   // [kGateBufs][H]
-    d2 *tab = buf + kGateBufs * kH;                      // [kTab9]
+    constexpr int ell = ELL;
+    const int K1 = a.k + 1, tid = threadIdx.x;
+    // LDS: accumulators [K1][N], y [kSlots][N], transforms [kGateBufs][H],
+    // twiddles [kTab9]
+    const uint32_t acc = 0, y = K1 * kRowBytes, buf = y + kSlots * kRowBytes;
+    d2 *tab = reinterpret_cast<d2 *>(smem + buf + kGateBufs * kBufBytes);
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid & 63;
     const int part = __builtin_amdgcn_readfirstlane(tid / 256);
     const int g = blockIdx.x;
     const uint32_t *abar = a.abar + (size_t)g * (a.k * a.n + 1);
     const Owner own(tid & 255, a.tab);
+    const Lane at(l);
     const int word = part * kH + (tid & 255);
     if (tid < kTab9) tab[tid] = a.tab[tid];
     load_acc<kGateT>(a, g, abar, acc);
@@ -609,55 +637,65 @@ __global__ __launch_bounds__(kGateT, 2) void fft_gate_kernel(FftArgs a) {
     __syncthreads();
     const KeyBlock ke(a.evk, K1 * ell, word);
     // keys [digit][j0]: d of the step, b of the first three slots
-    d2 xd[kEll][2], xe[kSlots][kEll][2];
+    d2 xd[ell][2], xe[kSlots][ell][2];
     auto load_d = [&](int step) {
         const KeyBlock kd(a.bk + (size_t)step * 3 * ell * kPoly, 3 * ell, word);
 #pragma unroll
-        for (int d = 0; d < kEll; ++d)
-            if (d < ell)
+        for (int d = 0; d < ell; ++d)
 #pragma unroll
                 for (int s = 0; s < 2; ++s) xd[d][s] = kd(d * kPoly + s * 256);
     };
-    auto load_e = [&](d2 (&x)[kEll][2], int j) {
+    auto load_e = [&](d2 (&x)[ell][2], int j) {
 #pragma unroll
-        for (int d = 0; d < kEll; ++d)
-            if (d < ell)
+        for (int d = 0; d < ell; ++d)
 #pragma unroll
                 for (int s = 0; s < 2; ++s) x[d][s] = ke((j * ell + d) * kPoly + s * 256);
     };
-    if (a.st0 < a.st1) load_d(a.st0);
-    int have = -1;   // party whose keys xe holds
+    auto load_step = [&](int step) {
+        const int party = step / a.n;
+        load_d(step);
+        load_e(xe[0], 0);
+        load_e(xe[1], 1 + party);
+    };
+    if (a.st0 < a.st1) load_step(a.st0);
     for (int step = a.st0; step < a.st1; ++step) {
         const int party = step / a.n;
         const int next_shift = step + 1 < a.st1 ? (int)abar[2 + step] : 0;
-        auto rot = [&](int row, int j) { rotate<kGateT>(acc + j * kN, shift, a.offset, here(tid), y + row * kN); };
+        auto rot = [&](int row, int j) { rotate<kGateT>(acc + j * kRowBytes, shift, a.offset, here(tid), y + row * kRowBytes); };
         Cx w[2] = {}, cA[2] = {}, cB[2] = {}, cT[2][2] = {};
         auto madd = [&](int i, const d2 (&x0)[2], Cx (&c0)[2], const d2 (&x1)[2], Cx (&c1)[2]) {
             Cx u, v;
-            own.get(buf + i * kH, u, v);
+            own.get(buf + i * kBufBytes, u, v);
             mac(c0[0], u, x0[0]);
             mac(c0[1], v, x0[1]);
             mac(c1[0], u, x1[0]);
             mac(c1[1], v, x1[1]);
         };
+        // touch the next step's keys, so that they are in this XCD's L2 by
+        // then (the keys of 4 parties and more exceed every cache)
+        uint32_t touched[3];
+        {
+            const uint32_t bytes = 3u * ell * kPoly * 16u;
+            const int nxt = min(step + 1, a.st1 - 1);
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(a.bk + (size_t)nxt * 3 * ell * kPoly), (short)0, (int)bytes, 0x00020000);
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                touched[i] = __builtin_amdgcn_raw_buffer_load_b32(r, 128u * (tid + kGateT * i), 0, 0);
+        }
         // slots 0, 1 + party and the first of the slots 1 .. party, which get
         // no stage-2 part; then those by twos
-        if (have != party) {
-            load_e(xe[0], 0);
-            load_e(xe[1], 1 + party);
-            if (party > 0) load_e(xe[2], 1);
-            have = party;
-        }
         rot(0, 0);
         rot(1, 1 + party);
         if (party > 0) rot(2, 1);
         lds_sync();
         for (int t = wave; t < (party > 0 ? 3 : 2) * ell; t += kGateW)
-            wave_fwd<false>(y + (t / ell) * kN, 24 - 8 * (t % ell), l, buf + t * kH, tab);
+            wave_fwd<false>(y + (t / ell) * kRowBytes, 24 - 8 * (t % ell), l, at, buf + t * kBufBytes, tab);
+        if (party > 0) load_e(xe[2], 1);
         lds_sync();
 #pragma unroll
-        for (int d = 0; d < kEll; ++d)
-            if (d < ell) {
+        for (int d = 0; d < ell; ++d)
+            {
                 madd(d, xe[0][d], w, xd[d], cA);
                 madd(ell + d, xe[1][d], w, xd[d], cB);
                 if (party > 0) madd(2 * ell + d, xe[2][d], w, xd[d], cT[0]);
@@ -669,23 +707,23 @@ __global__ __launch_bounds__(kGateT, 2) void fft_gate_kernel(FftArgs a) {
 #pragma unroll
             for (int i = 0; i < 2; ++i)
                 if (i < nT) {
-                    own.put(buf + (kFwd + 2 * i + part) * kH, cT[i]);
+                    own.put(buf + (kFwd + 2 * i + part) * kBufBytes, cT[i]);
                     cT[i][0] = cT[i][1] = {0.0, 0.0};
                 }
             for (int i = 0; i < cnt; ++i) rot(i, j0 + i);
             lds_sync();
             const int nf = cnt * ell, ni = nT * kParts, jT = done + 1 - nT;
             for (int t = wave; t < nf + ni; t += kGateW) {
-                if (t < nf) wave_fwd<false>(y + (t / ell) * kN, 24 - 8 * (t % ell), l, buf + t * kH, tab);
-                else wave_inv(buf + (kFwd + t - nf) * kH, acc + (jT + (t - nf) / 2) * kN, 16 * ((t - nf) & 1), l, tab);
+                if (t < nf) wave_fwd<false>(y + (t / ell) * kRowBytes, 24 - 8 * (t % ell), l, at, buf + t * kBufBytes, tab);
+                else wave_inv(buf + (kFwd + t - nf) * kBufBytes, acc + (jT + (t - nf) / 2) * kRowBytes, 16 * ((t - nf) & 1), l, at, tab);
             }
-            d2 xo[2][kEll][2];
+            d2 xo[2][ell][2];
             load_e(xo[0], j0);
             if (cnt > 1) load_e(xo[1], j0 + 1);
             lds_sync();
 #pragma unroll
-            for (int d = 0; d < kEll; ++d)
-                if (d < ell) {
+            for (int d = 0; d < ell; ++d)
+                {
                     madd(d, xo[0][d], w, xd[d], cT[0]);
                     if (cnt > 1) madd(ell + d, xo[1][d], w, xd[d], cT[1]);
                 }
@@ -695,46 +733,48 @@ __global__ __launch_bounds__(kGateT, 2) void fft_gate_kernel(FftArgs a) {
         // w, and the last slots without a stage-2 part
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-            if (i < nT) own.put(buf + (kFwd + 2 * i + part) * kH, cT[i]);
-        const int bw = nT == 2 ? 2 * kEll : kFwd + 2;   // free buffers
-        own.put(buf + (bw + part) * kH, w);
-        for (int i = tid; i < kN; i += kGateT) y[i] = a.offset;
+            if (i < nT) own.put(buf + (kFwd + 2 * i + part) * kBufBytes, cT[i]);
+        const int bw = nT == 2 ? 2 * ell : kFwd + 2;   // free buffers
+        own.put(buf + (bw + part) * kBufBytes, w);
+        for (int i = tid; i < kN; i += kGateT) stw(y + 4u * i, a.offset);
         lds_sync();
         if (wave < 2) {
-            wave_inv(buf + (bw + wave) * kH, y, 16 * wave, l, tab);
+            wave_inv(buf + (bw + wave) * kBufBytes, y, 16 * wave, l, at, tab);
         } else if (wave < 2 + nT * kParts) {
             const int t = wave - 2;
-            wave_inv(buf + (kFwd + t) * kH, acc + (done + 1 - nT + t / 2) * kN, 16 * (t & 1), l, tab);
+            wave_inv(buf + (kFwd + t) * kBufBytes, acc + (done + 1 - nT + t / 2) * kRowBytes, 16 * (t & 1), l, at, tab);
         }
-        d2 x0[kEll][2], x1[kEll][2];
-        {
+        d2 x0[ell][2], x1[ell][2];
+        auto load_f = [&]() {
             const KeyBlock kf(a.bk + ((size_t)step * 3 + 1) * ell * kPoly, 2 * ell, word);
 #pragma unroll
-            for (int d = 0; d < kEll; ++d)
-                if (d < ell)
+            for (int d = 0; d < ell; ++d)
 #pragma unroll
                     for (int s = 0; s < 2; ++s) {
                         x0[d][s] = kf(d * kPoly + s * 256);
                         x1[d][s] = kf((ell + d) * kPoly + s * 256);
                     }
-        }
+        };
+        
         lds_sync();
-        if (wave < ell) wave_fwd<true>(y, 24 - 8 * wave, l, buf + wave * kH, tab);
+        if (wave < ell) wave_fwd<true>(y, 24 - 8 * wave, l, at, buf + wave * kBufBytes, tab);
+        load_f();
         lds_sync();
 #pragma unroll
-        for (int d = 0; d < kEll; ++d)
-            if (d < ell) madd(d, x0[d], cA, x1[d], cB);
-        own.put(buf + (kFwd + part) * kH, cA);
-        own.put(buf + (kFwd + 2 + part) * kH, cB);
+        for (int d = 0; d < ell; ++d)
+            madd(d, x0[d], cA, x1[d], cB);
+        own.put(buf + (kFwd + part) * kBufBytes, cA);
+        own.put(buf + (kFwd + 2 + part) * kBufBytes, cB);
         lds_sync();
         if (wave < 4)
-            wave_inv(buf + (kFwd + wave) * kH, acc + (wave < 2 ? 0 : 1 + party) * kN, 16 * (wave & 1), l, tab);
-        load_d(min(step + 1, a.st1 - 1));
+            wave_inv(buf + (kFwd + wave) * kBufBytes, acc + (wave < 2 ? 0 : 1 + party) * kRowBytes, 16 * (wave & 1), l, at, tab);
+        load_step(min(step + 1, a.st1 - 1));
+        asm volatile("" : : "v"(touched[0]), "v"(touched[1]), "v"(touched[2]));
         shift = next_shift;
         lds_sync();
     }
     __syncthreads();
-    for (int idx = tid; idx < K1 * kN; idx += kGateT) a.acc[(size_t)g * K1 * kN + idx] = acc[idx];
+    for (int idx = tid; idx < K1 * kN; idx += kGateT) a.acc[(size_t)g * K1 * kN + idx] = ldw(acc + 4u * idx);
 }
 
 size_t fft_gate_lds(int k) {
@@ -748,8 +788,8 @@ static bool fft_supported(const mk_params &P) { return P.N == kN && P.bk_ell <= 
 // Automatic schedule, unless the caller forces something that only the int8
 // kernels have (GEMM tile shapes, team sizes): at N = 1024 the transforms are
 // faster at every batch size and party count (ms, int8 kernels / here: one
-// gate 34 / 9.4, 256 gates 45 / 9.4, 1024 gates 86 / 32.5 at 2 parties; 1024
-// gates 199 / 93 at 4 parties; 64 gates 180 / 96 at 8 parties).
+// gate 34 / 9.5, 256 gates 45 / 9.5, 1024 gates 86 / 32.4 at 2 parties; 1024
+// gates 199 / 89 at 4 parties; 64 gates 180 / 61 at 8 parties).
 bool use_fft(const mk_ctx *ctx) {
     const DeviceKeys &D = ctx->dev;
     return D.fft_bk && D.rot_kind == MK_ROT_AUTO && !D.team_rows && D.force_tiles[0] < 0 && D.force_tiles[1] < 0;
@@ -797,10 +837,10 @@ int fft_upload(mk_ctx *ctx, hipStream_t s) {
         return fail(MK_ENOMEM, "device allocation failed: transform tables");
     }
     MK_HIP(hipMemcpyAsync(D.fft_tab, tab.data(), tab.size() * sizeof(d2), hipMemcpyHostToDevice, s), "transform tables");
-    hipLaunchKernelGGL(fft_key_kernel, dim3((unsigned)bk_polys), dim3(256), 0, s, D.bk_ext, (const d2 *)D.fft_tab,
+    hipLaunchKernelGGL(fft_key_kernel, dim3((unsigned)bk_polys), dim3(256), kParts * kBufBytes, s, D.bk_ext, (const d2 *)D.fft_tab,
                        (d2 *)D.fft_bk);
     MK_HIP(hipGetLastError(), "bootstrapping key transform launch");
-    hipLaunchKernelGGL(fft_key_kernel, dim3((unsigned)evk_polys), dim3(256), 0, s, D.evk_ext, (const d2 *)D.fft_tab,
+    hipLaunchKernelGGL(fft_key_kernel, dim3((unsigned)evk_polys), dim3(256), kParts * kBufBytes, s, D.evk_ext, (const d2 *)D.fft_tab,
                        (d2 *)D.fft_evk);
     MK_HIP(hipGetLastError(), "evaluation key transform launch");
     MK_HIP(hipStreamSynchronize(s), "key transform sync");
@@ -808,12 +848,18 @@ int fft_upload(mk_ctx *ctx, hipStream_t s) {
 }
 
 template <class Kernel>
-static int launch_rotation(Kernel kern, int threads, size_t lds, const FftArgs &a, hipStream_t s) {
+static int launch_kernel(Kernel kern, int threads, size_t lds, const FftArgs &a, hipStream_t s) {
     MK_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
            "transform rotation LDS attribute");
     hipLaunchKernelGGL(kern, dim3((unsigned)a.G), dim3(threads), lds, s, a);
     MK_HIP(hipGetLastError(), "transform rotation launch");
     return MK_OK;
+}
+template <int ELL>
+static int launch_ell(const FftArgs &a, bool lean, hipStream_t s) {
+    if (lean) return launch_kernel(fft_lean_kernel<ELL>, kLeanT, fft_lean_lds(a.k), a, s);
+    if (a.k > 2) return launch_kernel(fft_gate_kernel<ELL, true>, kGateT, fft_gate_lds(a.k), a, s);
+    return launch_kernel(fft_gate_kernel<ELL, false>, kGateT, fft_gate_lds(a.k), a, s);
 }
 
 int launch_br_fft(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc, size_t count, int steps, hipStream_t s) {
@@ -828,23 +874,22 @@ int launch_br_fft(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc, size_t count
     StageTimer t1(ctx, 1, s);
     StageTimer t4(ctx, 4, s);
     // Which kernel: one gate per compute unit at a time, or several.  Measured
-    // on MI355X (256 compute units), fft_gate_kernel / fft_lean_kernel, ms:
-    // 2 parties 1 gate 9.4 / 17.5, 256 gates 9.4 / 16.9, 512 gates 18.5 / 21.2,
-    // 1024 gates 36.9 / 32.5; 4 parties 256 gates 41.2 / 41.2, 300 gates
-    // 88.6 / 53.2, 1024 gates 197 / 93; 8 parties 64 gates 96 / 113, 256 gates
-    // 118 / 116, 512 gates 235 / 150.
+    // on MI355X (256 compute units), fft_gate_kernel / fft_lean_kernel, ms: 2
+    // parties 256 gates 9.4 / 16.9, 512 gates 18.4 / 21.2, 1024 gates 36.8 /
+    // 32.4; 4 parties 256 gates 22.7 / 41, 512 gates 45 / 50, 1024 gates 91 /
+    // 89; 8 parties (two lean workgroups fit a compute unit) 256 gates 61 / 116,
+    // 512 gates 122 / 143.
     const size_t cus = (size_t)std::max(1, D.num_cus);
-    const bool lean = count > (P.k <= 2 ? 2 * cus : cus);
+    const bool lean = P.k <= 4 && count > 2 * cus;
     // During a capture a launch ends where the stream-ordered steps (four kernels
     // each) would end a graph piece, so pieces stay as long as documented.
     for (int st = 0; st < steps || st == 0; st = std::max(a.st1, 1)) {
         const int room = capture_room(ctx);
         a.st0 = st;
         a.st1 = room == INT_MAX ? steps : std::min(steps, st + (room + 3) / 4);
-        int rc;
-        if (lean) rc = launch_rotation(fft_lean_kernel, kLeanT, fft_lean_lds(P.k), a, s);
-        else if (P.k > 2) rc = launch_rotation(fft_gate_kernel<true>, kGateT, fft_gate_lds(P.k), a, s);
-        else rc = launch_rotation(fft_gate_kernel<false>, kGateT, fft_gate_lds(P.k), a, s);
+        int rc = P.bk_ell == 3   ? launch_ell<3>(a, lean, s)
+                 : P.bk_ell == 2 ? launch_ell<2>(a, lean, s)
+                                 : launch_ell<1>(a, lean, s);
         if (!rc) rc = capture_checkpoint(ctx, s, 4 * (a.st1 - a.st0));
         if (rc) return rc;
     }
