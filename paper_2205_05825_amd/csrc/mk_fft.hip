@@ -9,8 +9,10 @@
 // and nine levels split X^m = e^(i theta) into X^{m/2} = +- e^(i theta/2).  A
 // CMux step with L live slots then costs (L + 1) ell forward and 2 (L + 1)
 // inverse transforms and (4 L + 4) ell N/2 complex multiply-adds instead of
-// (8 L + 8) ell N^2 int8 operations, and each gate's accumulator stays in one
-// workgroup's LDS, so no workgroup ever waits for another.
+// (8 L + 8) ell N^2 int8 operations, and each gate's accumulator stays in LDS.
+// Three kernels: several gates per compute unit (fft_lean_kernel), one
+// (fft_gate_kernel), and several compute units per gate (fft_team_kernel, the
+// only one whose workgroups wait for each other).
 //
 // Exactness.  A key coefficient is split K = 2^16 K_hi + K_lo with signed
 // 16-bit halves; every accumulated product sum is then an integer below
@@ -76,7 +78,11 @@ constexpr double kMagic = 6755399441055744.0;   // 1.5 * 2^52
 
 // Twiddle table (complex words of (cos, tan) pairs): levels 4 and 5 by lane /
 // 16, four each; levels 6-8, four entries of 64 lanes; level 9 by thread.
-constexpr int kTabP = 0, kTabQ = 16, kTab9 = kTabQ + 256, kTabWords = kTab9 + 256;
+constexpr int kTabP = 0, kTabQ = 16, kTab9 = kTabQ + 256;
+// The same for transforms by a wave pair: levels 3 and 4 by lane / 16, two
+// each; levels 5 and 6, 16 entries each; levels 7 and 8, 128 each.
+constexpr int kTab2 = kTab9 + 256, kTab2Q = 8, kTab2R = kTab2Q + 32, kTab2Words = kTab2R + 256;
+constexpr int kTabWords = kTab2 + kTab2Words;
 
 struct Cx {
     double r, i;
@@ -381,6 +387,197 @@ __device__ __forceinline__ void wave_inv(uint32_t buf, uint32_t dst, int sh, int
     }
 }
 
+// ------------------------------------------- transforms by a wave pair ----
+//
+// For short latency: 128 lanes hold four points each, the exchange through LDS
+// is between the two waves, and every transform has two halves with a
+// workgroup barrier between them.  Per wave half the arithmetic and half the
+// LDS words of a transform by one wave: where compute units have few
+// transforms at a time one takes 2.2k cycles instead of 2.8k (team kernel, one
+// gate at 2 parties 8.2 -> 7.6 ms), with nine at a time they are bound by
+// instruction issue either way (gate kernel, 9.4 -> 8.9 ms at 2 parties).  A wave's inner and hand-over words are
+// the same half of the buffer (j8), so neither wave overwrites words that the
+// other has yet to read.
+
+struct Lane2 {
+    uint32_t e, h;   // exchange (outer | inner << 16) and hand-over (inner)
+    uint32_t io;     // words: of y (packed order) | of an accumulator << 16
+    __device__ __forceinline__ Lane2(int l, int w) {
+        {   // outer: lane (j8 j7 j3 j2 j1 j0), wave j4, registers (j6 j5)
+            const int j7 = (l >> 4) & 1;
+            e = 16u * (uint32_t)((l >> 4) * 128 + w * 16 + ((l & 15) ^ (j7 << 1)));
+            // before the permutes: lane (j6 j5 j3 j2 j1 j0), registers (j8 j7)
+            io = 4u * (uint32_t)(w * 64 + l) | (4u * (uint32_t)((l >> 4) * 32 + w * 16 + (l & 15))) << 16;
+        }
+        {   // inner: lane (j2 j1 j5 j6 j7 j0), wave j8, registers (j4 j3); after
+            // the permutes lane (j4 j3 j5 j6 j7 j0), registers (j2 j1)
+            const int j0 = l & 1, j7 = (l >> 1) & 1, j6 = (l >> 2) & 1, j5 = (l >> 3) & 1, x4 = (l >> 4) & 1, x5 = l >> 5;
+            const int b4 = w * 8 + j7 * 4 + j6 * 2 + j5;
+            e |= 16u * (uint32_t)(b4 * 32 + ((j5 << 3) ^ ((x5 ^ j6) << 2) ^ ((x4 ^ j7) << 1) ^ j0)) << 16;
+            h = 16u * (uint32_t)(w * 256 + j0 * 128 + (b4 & 7) * 16 + ((x5 ^ j6) << 3) + ((x4 ^ j6) << 2) + (j7 << 1) + j0);
+        }
+    }
+    __device__ __forceinline__ Lane2 here() const {
+        Lane2 v = *this;
+        asm volatile("" : "+v"(v.e), "+v"(v.h), "+v"(v.io));
+        return v;
+    }
+    __device__ __forceinline__ uint32_t outer(uint32_t buf, int r) const {   // r = (j6 j5)
+        return ((buf + (e & 0xFFFFu)) ^ (uint32_t)((r & 1) * 128 + (r >> 1) * 64)) + (uint32_t)((r >> 1) * 1024 + (r & 1) * 512);
+    }
+    __device__ __forceinline__ uint32_t inner(uint32_t buf, int r) const {   // r = (j4 j3)
+        return ((buf + (e >> 16)) ^ (uint32_t)((r & 1) * 128)) + (uint32_t)((r >> 1) * 256);
+    }
+    __device__ __forceinline__ uint32_t hand(uint32_t buf, int r) const { return (buf + h) ^ (uint32_t)(16 * r); }   // (j2 j1)
+};
+// Byte of coefficient m in y's order (j4 above j6)
+__device__ __forceinline__ uint32_t packed_byte(int m) {
+    return 4u * (uint32_t)((m & ~0x70) | ((m & 0x10) << 2) | ((m & 0x60) >> 1));
+}
+// Hand-over word of thread c = (j8 .. j1), j0 = 0 (j0 = 1: 128 + (word ^ 1))
+__device__ __forceinline__ int owner_word2(int c) {
+    const int j7 = (c >> 6) & 1, j6 = (c >> 5) & 1;
+    return ((c & 128) << 1) | ((c & 127) ^ (j7 << 1) ^ (j6 << 2) ^ (j6 << 3));
+}
+
+// Coefficients from y, in y's order; FLIP: they still have their bias.
+template <bool FLIP>
+struct FromY {
+    uint32_t y;
+    __device__ __forceinline__ void operator()(const Lane2 &at, int r, uint32_t &a, uint32_t &b) const {
+        const uint32_t yl = y + (at.io & 0xFFFFu);
+        a = ldw(yl + 512u * r);
+        b = ldw(yl + 512u * r + kRowBytes / 2);
+        if constexpr (FLIP) {
+            a ^= 0x80808080u;
+            b ^= 0x80808080u;
+        }
+    }
+};
+// `words(at, r, a, b)`: biased coefficients 128 r + .. and 512 + 128 r + ..
+template <class Words>
+__device__ __forceinline__ void pair_fwd_a(Words words, int sh, int lane, const Lane2 &lane_at, uint32_t buf, const d2 *tab2) {
+    const int l = here(lane);
+    const Lane2 at = lane_at.here();
+    const d2 t3 = tab2[(l >> 4) * 2], t4 = tab2[(l >> 4) * 2 + 1];
+    Cx x[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        uint32_t a, b;
+        words(at, r, a, b);
+        x[r].r = (double)(int)__builtin_amdgcn_sbfe(a, sh, 8);
+        x[r].i = (double)(int)__builtin_amdgcn_sbfe(b, sh, 8);
+    }
+    bf_fwd<false>(x[0], x[2], kTwA[0].c, kTwA[0].t);
+    bf_fwd<false>(x[1], x[3], kTwA[0].c, kTwA[0].t);
+    bf_fwd<false>(x[0], x[1], kTwA[1].c, kTwA[1].t);
+    bf_fwd<true>(x[2], x[3], kTwA[1].c, kTwA[1].t);
+    swap_bit<32>(x[0], x[2]);
+    swap_bit<32>(x[1], x[3]);
+    bf_fwd<false>(x[0], x[2], t3.x, t3.y);
+    bf_fwd<true>(x[1], x[3], t3.x, t3.y);
+    swap_bit<16>(x[0], x[1]);
+    swap_bit<16>(x[2], x[3]);
+    bf_fwd<false>(x[0], x[1], t4.x, t4.y);
+    bf_fwd<true>(x[2], x[3], t4.x, t4.y);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) st(at.outer(buf, r), x[r]);
+}
+__device__ __forceinline__ void pair_fwd_b(int lane, int w, const Lane2 &lane_at, uint32_t buf, const d2 *tab2) {
+    const int l = here(lane);
+    const Lane2 at = lane_at.here();
+    Cx x[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = ld(at.inner(buf, r));
+    const d2 *tq = tab2 + kTab2Q + w * 8 + ((l >> 1) & 7), *tr = tab2 + kTab2R + w * 64 + l;
+    const d2 t5 = tq[0], t6 = tq[16], t7 = tr[0], t8 = tr[128];
+    bf_fwd<false>(x[0], x[2], t5.x, t5.y);
+    bf_fwd<false>(x[1], x[3], t5.x, t5.y);
+    bf_fwd<false>(x[0], x[1], t6.x, t6.y);
+    bf_fwd<true>(x[2], x[3], t6.x, t6.y);
+    swap_bit<32>(x[0], x[2]);
+    swap_bit<32>(x[1], x[3]);
+    bf_fwd<false>(x[0], x[2], t7.x, t7.y);
+    bf_fwd<true>(x[1], x[3], t7.x, t7.y);
+    swap_bit<16>(x[0], x[1]);
+    swap_bit<16>(x[2], x[3]);
+    bf_fwd<false>(x[0], x[1], t8.x, t8.y);
+    bf_fwd<true>(x[2], x[3], t8.x, t8.y);
+    wave_fence();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) st(at.hand(buf, r), x[r]);
+}
+__device__ __forceinline__ void pair_inv_a(int lane, int w, const Lane2 &lane_at, uint32_t buf, const d2 *tab2) {
+    const int l = here(lane);
+    const Lane2 at = lane_at.here();
+    Cx x[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = ld(at.hand(buf, r));
+    const d2 *tq = tab2 + kTab2Q + w * 8 + ((l >> 1) & 7), *tr = tab2 + kTab2R + w * 64 + l;
+    const d2 t5 = tq[0], t6 = tq[16], t7 = tr[0], t8 = tr[128];
+    bf_inv<false, true>(x[0], x[1], t8.x, t8.y);
+    bf_inv<true, true>(x[2], x[3], t8.x, t8.y);
+    swap_bit<16>(x[0], x[1]);
+    swap_bit<16>(x[2], x[3]);
+    bf_inv<false, true>(x[0], x[2], t7.x, t7.y);
+    bf_inv<true, true>(x[1], x[3], t7.x, t7.y);
+    swap_bit<32>(x[0], x[2]);
+    swap_bit<32>(x[1], x[3]);
+    bf_inv<false, true>(x[0], x[1], t6.x, t6.y);
+    bf_inv<true, true>(x[2], x[3], t6.x, t6.y);
+    bf_inv<false, true>(x[0], x[2], t5.x, t5.y);
+    bf_inv<false, true>(x[1], x[3], t5.x, t5.y);
+    wave_fence();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) st(at.inner(buf, r), x[r]);
+}
+// Where an inverse's words go: added to an accumulator row or (packed) to y, or
+// stored in y.
+struct Add {
+    uint32_t dst;
+    bool packed;
+    __device__ __forceinline__ void operator()(const Lane2 &at, int r, uint32_t a, uint32_t b) const {
+        const uint32_t dl = dst + (packed ? at.io & 0xFFFFu : at.io >> 16);
+        addw(dl + 512u * r, a);
+        addw(dl + 512u * r + kRowBytes / 2, b);
+    }
+};
+struct SetY {
+    uint32_t dst;
+    __device__ __forceinline__ void operator()(const Lane2 &at, int r, uint32_t a, uint32_t b) const {
+        const uint32_t dl = dst + (at.io & 0xFFFFu);
+        stw(dl + 512u * r, a);
+        stw(dl + 512u * r + kRowBytes / 2, b);
+    }
+};
+
+template <class Out>
+__device__ __forceinline__ void pair_inv_b(uint32_t buf, Out out, int sh, int lane, const Lane2 &lane_at, const d2 *tab2) {
+    const int l = here(lane);
+    const Lane2 at = lane_at.here();
+    Cx x[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = ld(at.outer(buf, r));
+    const d2 t3 = tab2[(l >> 4) * 2], t4 = tab2[(l >> 4) * 2 + 1];
+    bf_inv<false, true>(x[0], x[1], t4.x, t4.y);
+    bf_inv<true, true>(x[2], x[3], t4.x, t4.y);
+    swap_bit<16>(x[0], x[1]);
+    swap_bit<16>(x[2], x[3]);
+    bf_inv<false, true>(x[0], x[2], t3.x, t3.y);
+    bf_inv<true, true>(x[1], x[3], t3.x, t3.y);
+    swap_bit<32>(x[0], x[2]);
+    swap_bit<32>(x[1], x[3]);
+    bf_inv<false, false>(x[0], x[1], kTwA[1].c, kTwA[1].t);
+    bf_inv<true, false>(x[2], x[3], kTwA[1].c, kTwA[1].t);
+    bf_inv<false, false>(x[0], x[2], kTwA[0].c, kTwA[0].t);
+    bf_inv<false, false>(x[1], x[3], kTwA[0].c, kTwA[0].t);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const double s = (1.0 / kH) * ((r & 1) ? kTwA[1].c : 1.0) * ((r & 2) ? kTwA[0].c : 1.0);
+        out(at, r, round_word(x[r].r, s) << sh, round_word(x[r].i, s) << sh);
+    }
+}
+
 __device__ __forceinline__ void mac(Cx &s, const Cx &u, const d2 &k) {
     s.r = __builtin_fma(u.r, k.x, __builtin_fma(-u.i, k.y, s.r));
     s.i = __builtin_fma(u.r, k.y, __builtin_fma(u.i, k.x, s.i));
@@ -440,6 +637,10 @@ struct FftArgs {
     const d2 *bk;           // [k][n][3][ell][part][j0][256]
     const d2 *evk;          // [k+1][ell][part][j0][256]
     const d2 *tab;
+    // teams (fft_team_kernel)
+    uint64_t *xch;          // boxes [G][members][2][N]
+    uint32_t *status;
+    int members, nx;
 };
 
 // Accumulators of one gate: X^-b v, 0, .. at the start, else the rows saved before.
@@ -460,22 +661,36 @@ __device__ __forceinline__ void load_acc(const FftArgs &a, int g, const uint32_t
 }
 
 // X^-shift c - c into y, biased for digit extraction.
-template <int T>
+template <int T, bool PACKED>
 __device__ __forceinline__ void rotate(uint32_t c, int shift, uint32_t offset, int tid, uint32_t y) {
 #pragma unroll
     for (int i = 0; i < kN / T; ++i) {
         const int m = tid + T * i, s = m + shift;
         const uint32_t src = ldw(c + 4u * (uint32_t)(s & (kN - 1))), rot = (s & kN) ? 0u - src : src;
-        stw(y + 4u * m, (rot - ldw(c + 4u * m) + offset) ^ 0x80808080u);
+        stw(y + (PACKED ? packed_byte(m) : 4u * m), (rot - ldw(c + 4u * m) + offset) ^ 0x80808080u);
     }
 }
+
+// Rotation amounts of the next 64 steps, one per lane: a load per step would
+// have to wait for the key loads in flight before it.
+struct Shifts {
+    const uint32_t *abar;   // of step 0
+    int end, lane;
+    uint32_t v;
+    __device__ __forceinline__ int operator()(int step, int first) {
+        const int i = (step - first) & 63;
+        if (i == 0) v = abar[min(step + lane, end - 1)];
+        return (int)__builtin_amdgcn_readlane(v, i);
+    }
+};
 
 // The thread's two frequencies of the transform in `buf`, and back.
 struct Owner {
     uint32_t at0, at1;
     double c, t;
-    __device__ __forceinline__ Owner(int c_, const d2 *tab)
-        : at0(16u * owner_word(c_)), at1(4096u + (16u * owner_word(c_) ^ 16u)) {
+    // hand-over words of j0 = 0 and, `apart` words on, of j0 = 1
+    __device__ __forceinline__ Owner(int c_, int word, int apart, const d2 *tab)
+        : at0(16u * (uint32_t)word), at1(16u * (uint32_t)(apart + (word ^ 1))) {
         const d2 v = tab[kTab9 + c_];
         c = v.x;
         t = v.y;
@@ -506,7 +721,7 @@ __global__ __launch_bounds__(kLeanT, 4) void fft_lean_kernel(FftArgs a) {
     const int g = blockIdx.x;
     const uint32_t *abar = a.abar + (size_t)g * (a.k * a.n + 1);
     const d2 *tab = a.tab;
-    const Owner own(tid, tab);
+    const Owner own(tid, owner_word(tid), 256, tab);
     const Lane at(l);
     load_acc<kLeanT>(a, g, abar, acc);
     int shift = a.st0 < a.st1 ? (int)abar[1 + a.st0] : 0;
@@ -516,7 +731,7 @@ __global__ __launch_bounds__(kLeanT, 4) void fft_lean_kernel(FftArgs a) {
         const int party = step / a.n, bit = step - party * a.n;
         const int next_shift = step + 1 < a.st1 ? (int)abar[2 + step] : 0;
         const KeyBlock kd(a.bk + ((size_t)party * a.n + bit) * 3 * ell * kPoly, 3 * ell, tid), ke(a.evk, K1 * ell, tid);
-        auto rot = [&](int j) { rotate<kLeanT>(acc + j * kRowBytes, shift, a.offset, here(tid), y); };
+        auto rot = [&](int j) { rotate<kLeanT, false>(acc + j * kRowBytes, shift, a.offset, here(tid), y); };
         // products of the ell transforms with two key polynomials each
         auto madd = [&](const KeyBlock &k0, int p0, Cx (&c0)[kParts][2], const KeyBlock &k1, int p1, Cx (&c1)[kParts][2]) {
             lds_sync();
@@ -609,29 +824,37 @@ __global__ __launch_bounds__(kLeanT, 4) void fft_lean_kernel(FftArgs a) {
 
 size_t fft_lean_lds(int k) { return (size_t)(k + 2) * kN * 4 + (size_t)kLeanBufs * kH * 16; }
 
-// One gate per compute unit.
+// One gate per compute unit.  Bound by the serial chain of a step (rotate,
+// digits forward, products, V back, forward, products, back: 18k cycles at two
+// parties), half of it instruction issue of the first transforms and products.
+// A word's two key parts are two threads', so that the keys of a step fit
+// registers and can be loaded a phase before their use, in small groups between
+// the transforms' halves: a wave that meets a full memory pipe stalls, whatever
+// it wanted to do next.  Measured (2 / 4 parties, up to 256 gates): 8.8 / 22.3
+// ms; 9.4 / 22.7 with transforms by single waves and keys loaded in one go.
 constexpr int kGateT = 512;           // threads: part tid / 256 of word tid % 256
-constexpr int kGateW = kGateT / 64;   // waves
+constexpr int kGateP = kGateT / 128;  // wave pairs
 constexpr int kSlots = 3;             // slots whose digits are transformed together
 constexpr int kFwd = kSlots * kEll;   // buffers of digit transforms
 constexpr int kGateBufs = kFwd + 4;   // and of inverse transforms
 
-template <int ELL, bool MANY>
+template <int ELL>
 __global__ __launch_bounds__(kGateT, 2) void fft_gate_kernel(FftArgs a) {
     constexpr int ell = ELL;
     const int K1 = a.k + 1, tid = threadIdx.x;
     // LDS: accumulators [K1][N], y [kSlots][N], transforms [kGateBufs][H],
-    // twiddles [kTab9]
+    // twiddles [kTab2Words]
     const uint32_t acc = 0, y = K1 * kRowBytes, buf = y + kSlots * kRowBytes;
     d2 *tab = reinterpret_cast<d2 *>(smem + buf + kGateBufs * kBufBytes);
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid & 63;
     const int part = __builtin_amdgcn_readfirstlane(tid / 256);
     const int g = blockIdx.x;
     const uint32_t *abar = a.abar + (size_t)g * (a.k * a.n + 1);
-    const Owner own(tid & 255, a.tab);
-    const Lane at(l);
+    const Owner own(tid & 255, owner_word2(tid & 255), 128, a.tab);
+    const int pair = wave >> 1, w2 = wave & 1;
+    const Lane2 at(l, w2);
     const int word = part * kH + (tid & 255);
-    if (tid < kTab9) tab[tid] = a.tab[tid];
+    if (tid < kTab2Words) tab[tid] = a.tab[kTab2 + tid];
     load_acc<kGateT>(a, g, abar, acc);
     int shift = a.st0 < a.st1 ? (int)abar[1 + a.st0] : 0;
     __syncthreads();
@@ -651,17 +874,14 @@ __global__ __launch_bounds__(kGateT, 2) void fft_gate_kernel(FftArgs a) {
 #pragma unroll
                 for (int s = 0; s < 2; ++s) x[d][s] = ke((j * ell + d) * kPoly + s * 256);
     };
-    auto load_step = [&](int step) {
-        const int party = step / a.n;
-        load_d(step);
+    if (a.st0 < a.st1) {
+        load_d(a.st0);
         load_e(xe[0], 0);
-        load_e(xe[1], 1 + party);
-    };
-    if (a.st0 < a.st1) load_step(a.st0);
+    }
     for (int step = a.st0; step < a.st1; ++step) {
         const int party = step / a.n;
-        const int next_shift = step + 1 < a.st1 ? (int)abar[2 + step] : 0;
-        auto rot = [&](int row, int j) { rotate<kGateT>(acc + j * kRowBytes, shift, a.offset, here(tid), y + row * kRowBytes); };
+        const int next = min(step + 1, a.st1 - 1);
+        auto rot = [&](int row, int j) { rotate<kGateT, true>(acc + j * kRowBytes, shift, a.offset, here(tid), y + row * kRowBytes); };
         Cx w[2] = {}, cA[2] = {}, cB[2] = {}, cT[2][2] = {};
         auto madd = [&](int i, const d2 (&x0)[2], Cx (&c0)[2], const d2 (&x1)[2], Cx (&c1)[2]) {
             Cx u, v;
@@ -671,26 +891,18 @@ __global__ __launch_bounds__(kGateT, 2) void fft_gate_kernel(FftArgs a) {
             mac(c1[0], u, x1[0]);
             mac(c1[1], v, x1[1]);
         };
-        // touch the next step's keys, so that they are in this XCD's L2 by
-        // then (the keys of 4 parties and more exceed every cache)
-        uint32_t touched[3];
-        {
-            const uint32_t bytes = 3u * ell * kPoly * 16u;
-            const int nxt = min(step + 1, a.st1 - 1);
-            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-                (void *)(a.bk + (size_t)nxt * 3 * ell * kPoly), (short)0, (int)bytes, 0x00020000);
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-                touched[i] = __builtin_amdgcn_raw_buffer_load_b32(r, 128u * (tid + kGateT * i), 0, 0);
-        }
         // slots 0, 1 + party and the first of the slots 1 .. party, which get
         // no stage-2 part; then those by twos
         rot(0, 0);
         rot(1, 1 + party);
         if (party > 0) rot(2, 1);
         lds_sync();
-        for (int t = wave; t < (party > 0 ? 3 : 2) * ell; t += kGateW)
-            wave_fwd<false>(y + (t / ell) * kRowBytes, 24 - 8 * (t % ell), l, at, buf + t * kBufBytes, tab);
+        const int nf = (party > 0 ? 3 : 2) * ell;
+        for (int t = pair; t < nf; t += kGateP)
+            pair_fwd_a(FromY<false>{y + (t / ell) * kRowBytes}, 24 - 8 * (t % ell), l, at, buf + t * kBufBytes, tab);
+        load_e(xe[1], 1 + party);
+        lds_sync();
+        for (int t = pair; t < nf; t += kGateP) pair_fwd_b(l, w2, at, buf + t * kBufBytes, tab);
         if (party > 0) load_e(xe[2], 1);
         lds_sync();
 #pragma unroll
@@ -702,7 +914,7 @@ __global__ __launch_bounds__(kGateT, 2) void fft_gate_kernel(FftArgs a) {
             }
         int done = 1;                  // slots 1 .. done are transformed;
         int nT = party > 0 ? 1 : 0;    // the last nT of them wait for their inverse
-        while (MANY && done < party) {
+        while (done < party) {
             const int cnt = min(2, party - done), j0 = done + 1;
 #pragma unroll
             for (int i = 0; i < 2; ++i)
@@ -712,10 +924,15 @@ __global__ __launch_bounds__(kGateT, 2) void fft_gate_kernel(FftArgs a) {
                 }
             for (int i = 0; i < cnt; ++i) rot(i, j0 + i);
             lds_sync();
-            const int nf = cnt * ell, ni = nT * kParts, jT = done + 1 - nT;
-            for (int t = wave; t < nf + ni; t += kGateW) {
-                if (t < nf) wave_fwd<false>(y + (t / ell) * kRowBytes, 24 - 8 * (t % ell), l, at, buf + t * kBufBytes, tab);
-                else wave_inv(buf + (kFwd + t - nf) * kBufBytes, acc + (jT + (t - nf) / 2) * kRowBytes, 16 * ((t - nf) & 1), l, at, tab);
+            const int mf = cnt * ell, mi = nT * kParts, jT = done + 1 - nT;
+            for (int t = pair; t < mf + mi; t += kGateP) {
+                if (t < mf) pair_fwd_a(FromY<false>{y + (t / ell) * kRowBytes}, 24 - 8 * (t % ell), l, at, buf + t * kBufBytes, tab);
+                else pair_inv_a(l, w2, at, buf + (kFwd + t - mf) * kBufBytes, tab);
+            }
+            lds_sync();
+            for (int t = pair; t < mf + mi; t += kGateP) {
+                if (t < mf) pair_fwd_b(l, w2, at, buf + t * kBufBytes, tab);
+                else pair_inv_b(buf + (kFwd + t - mf) * kBufBytes, Add{acc + (jT + (t - mf) / 2) * kRowBytes, false}, 16 * ((t - mf) & 1), l, at, tab);
             }
             d2 xo[2][ell][2];
             load_e(xo[0], j0);
@@ -738,39 +955,45 @@ __global__ __launch_bounds__(kGateT, 2) void fft_gate_kernel(FftArgs a) {
         own.put(buf + (bw + part) * kBufBytes, w);
         for (int i = tid; i < kN; i += kGateT) stw(y + 4u * i, a.offset);
         lds_sync();
-        if (wave < 2) {
-            wave_inv(buf + (bw + wave) * kBufBytes, y, 16 * wave, l, at, tab);
-        } else if (wave < 2 + nT * kParts) {
-            const int t = wave - 2;
-            wave_inv(buf + (kFwd + t) * kBufBytes, acc + (done + 1 - nT + t / 2) * kRowBytes, 16 * (t & 1), l, at, tab);
-        }
+        // transforms: w low, w high, then the slots'
+        const int ni = 2 + nT * kParts;
+        for (int t = pair; t < ni; t += kGateP) pair_inv_a(l, w2, at, buf + (t < 2 ? bw + t : kFwd + t - 2) * kBufBytes, tab);
         d2 x0[ell][2], x1[ell][2];
-        auto load_f = [&]() {
-            const KeyBlock kf(a.bk + ((size_t)step * 3 + 1) * ell * kPoly, 2 * ell, word);
+        const KeyBlock kf(a.bk + ((size_t)step * 3 + 1) * ell * kPoly, 2 * ell, word);
+        auto load_f = [&](int part_of) {
 #pragma unroll
             for (int d = 0; d < ell; ++d)
+                if (d == part_of)
 #pragma unroll
                     for (int s = 0; s < 2; ++s) {
                         x0[d][s] = kf(d * kPoly + s * 256);
                         x1[d][s] = kf((ell + d) * kPoly + s * 256);
                     }
         };
-        
+        load_f(0);
         lds_sync();
-        if (wave < ell) wave_fwd<true>(y, 24 - 8 * wave, l, at, buf + wave * kBufBytes, tab);
-        load_f();
+        for (int t = pair; t < ni; t += kGateP)
+            pair_inv_b(buf + (t < 2 ? bw + t : kFwd + t - 2) * kBufBytes, Add{t < 2 ? y : acc + (done + 1 - nT + (t - 2) / 2) * kRowBytes, t < 2}, 16 * (t & 1), l, at, tab);
+        load_f(1);
         lds_sync();
+        if (pair < ell) pair_fwd_a(FromY<true>{y}, 24 - 8 * pair, l, at, buf + pair * kBufBytes, tab);
+        load_f(2);
+        lds_sync();
+        if (pair < ell) pair_fwd_b(l, w2, at, buf + pair * kBufBytes, tab);
+        lds_sync();
+        const int next_shift = (int)abar[1 + next];
 #pragma unroll
         for (int d = 0; d < ell; ++d)
             madd(d, x0[d], cA, x1[d], cB);
         own.put(buf + (kFwd + part) * kBufBytes, cA);
         own.put(buf + (kFwd + 2 + part) * kBufBytes, cB);
         lds_sync();
-        if (wave < 4)
-            wave_inv(buf + (kFwd + wave) * kBufBytes, acc + (wave < 2 ? 0 : 1 + party) * kRowBytes, 16 * (wave & 1), l, at, tab);
-        load_step(min(step + 1, a.st1 - 1));
-        asm volatile("" : : "v"(touched[0]), "v"(touched[1]), "v"(touched[2]));
-        shift = next_shift;
+        pair_inv_a(l, w2, at, buf + (kFwd + pair) * kBufBytes, tab);
+        load_d(next);
+        lds_sync();
+        pair_inv_b(buf + (kFwd + pair) * kBufBytes, Add{acc + (pair < 2 ? 0 : 1 + party) * kRowBytes, false}, 16 * (pair & 1), l, at, tab);
+        load_e(xe[0], 0);
+        shift = __builtin_amdgcn_readfirstlane(next_shift);
         lds_sync();
     }
     __syncthreads();
@@ -778,7 +1001,245 @@ __global__ __launch_bounds__(kGateT, 2) void fft_gate_kernel(FftArgs a) {
 }
 
 size_t fft_gate_lds(int k) {
-    return (size_t)(k + 1 + kSlots) * kN * 4 + (size_t)(kGateBufs * kH + kTab9) * 16;
+    return (size_t)(k + 1 + kSlots) * kN * 4 + (size_t)(kGateBufs * kH + kTab2Words) * 16;
+}
+
+// A team of workgroups per gate, for batches that leave compute units idle.
+// Members 0 and 1 own the slots with a stage-2 part (0 and 1 + party), helpers
+// up to three of the slots 1 .. party each (members 0 and 1 what is left): a
+// member rotates, transforms and multiplies its own slots, turns its own sum of
+// products into its part of V (an integer, so the parts add exactly), and
+// publishes it.  Members 0 and 1 add the parts up and run stage 2 of their
+// slot.  Nothing else is exchanged, once per step; helpers need no V, so they
+// run up to a step ahead.  A launch ends with a party, since slots then change
+// hands.
+//
+// A published word is 64 bits, value and step number, written and read
+// atomically at device scope: it is either not there yet or complete, and no
+// other ordering is needed.  A box has two sides by the step's parity.  Members
+// 0 and 1 publish step s only after reading step s - 1, so whoever has seen
+// their step s may overwrite the side of step s - 1 (their own words for
+// members 0 and 1, which read every step; `passed` for helpers).  Waits are
+// bounded (kSpinLimit): a member that gives up sets the status word, waits no
+// more and goes on publishing, so every workgroup ends.  A team's blocks are
+// nx apart, hence on one XCD and next to each other in its dispatch order, and
+// the team size is chosen so that all are resident at once on an idle device:
+// on a busy one a team waits until earlier work leaves room for its last member.
+//
+// Bound by the latency of four transforms (2.2k cycles each), two rounds of
+// products (1.2k) and the exchange (2.2-3k, of which a load is 1.1k).  Measured
+// (ms, one workgroup per gate / here): one gate at 2, 4, 8 parties 8.8 / 7.3,
+// 22.3 / 15.7, 64 / 30.7; 64 gates at 8 parties 64 / 35.4.
+struct Team {
+    int m, helpers, party;
+    __device__ __forceinline__ int slots() const {
+        const int q = min(party, kSlots * helpers);   // helpers' slots
+        if (m >= 2) return (q - (m - 2) + helpers - 1) / helpers;
+        return 1 + (party - q - m + 1) / 2;
+    }
+    __device__ __forceinline__ int slot(int i) const {
+        if (m >= 2) return 1 + (m - 2) + i * helpers;
+        return i == 0 ? m * (1 + party) : 1 + kSlots * helpers + m + 2 * (i - 1);
+    }
+    __device__ __forceinline__ bool owns(int j) const {
+        for (int i = 0; i < slots(); ++i)
+            if (slot(i) == j) return true;
+        return m == 0 && j > 1 + party;   // rows still zero
+    }
+};
+
+// What a team exchanges: a value and its tag in one 64-bit word, so that a word
+// is either not there yet or complete.
+struct Box {
+    uint64_t *p;
+    __device__ __forceinline__ static uint64_t get(uint64_t *q) {
+        // read where atomics are done: 64 gates at 8 parties 37.7 -> 36.7 ms
+        // against a device-scope load
+        return __hip_atomic_fetch_or(q, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ static void put(uint64_t *q, uint32_t v, uint32_t tag) {
+        __hip_atomic_store(q, (uint64_t)tag << 32 | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ u4 load(uint32_t off) const {
+        const uint64_t v = get(p + off / 8), u = get(p + off / 8 + 1);
+        return u4{(uint32_t)v, (uint32_t)(v >> 32), (uint32_t)u, (uint32_t)(u >> 32)};
+    }
+    __device__ __forceinline__ void store(uint32_t off, u4 v) const {
+        put(p + off / 8, v.x, v.y);
+        put(p + off / 8 + 1, v.z, v.w);
+    }
+};
+constexpr int kMaxMembers = 5;
+constexpr uint32_t kBoxBytes = kN * 8;   // (value, tag) words of one member and parity
+
+constexpr uint32_t kSpinLimit = 1u << 23;   // polls of about a microsecond
+
+template <int ELL>
+__global__ __launch_bounds__(kGateT, 2) void fft_team_kernel(FftArgs a) {
+    constexpr int ell = ELL;
+    const int K1 = a.k + 1, tid = threadIdx.x;
+    // LDS as in fft_gate_kernel
+    const uint32_t acc = 0, y = K1 * kRowBytes, buf = y + kSlots * kRowBytes;
+    d2 *tab = reinterpret_cast<d2 *>(smem + buf + kGateBufs * kBufBytes);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid & 63;
+    const int part = __builtin_amdgcn_readfirstlane(tid / 256);
+    // blocks go round the XCDs: a team's members share an L2
+    const int x = blockIdx.x % a.nx, b = blockIdx.x / a.nx;
+    const int g = x + a.nx * (b / a.members);
+    const int party = a.st0 / a.n;
+    const Team team{b % a.members, a.members - 2, party};
+    if (g >= a.G) return;
+    const int ns = team.slots();
+    if (ns <= 0) return;
+    const int helpers = min(party, a.members - 2);   // that own a slot
+    const int members = 2 + helpers;
+    const bool helper = team.m >= 2;
+    const uint32_t *abar = a.abar + (size_t)g * (a.k * a.n + 1);
+    const int pair = wave >> 1, w2 = wave & 1;
+    const Owner own(tid & 255, owner_word2(tid & 255), 128, a.tab);
+    const Lane2 at(l, w2);
+    const int word = part * kH + (tid & 255);
+    if (tid < kTab2Words) tab[tid] = a.tab[kTab2 + tid];
+    load_acc<kGateT>(a, g, abar, acc);
+    __syncthreads();
+    const KeyBlock ke(a.evk, K1 * ell, word);
+    d2 xd[ell][2], xe[kSlots][ell][2], xf[ell][2];
+    auto load = [&](d2 (&v)[ell][2], const KeyBlock &k, int poly) {
+#pragma unroll
+        for (int d = 0; d < ell; ++d)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) v[d][s] = k((poly + d) * kPoly + s * 256);
+    };
+    auto keys = [&](int step) { return KeyBlock(a.bk + (size_t)step * 3 * ell * kPoly, 3 * ell, word); };
+    load(xd, keys(a.st0), 0);
+    load(xe[0], ke, team.slot(0) * ell);
+    Shifts shifts{abar + 1, a.st1, l, 0};
+    bool dead = false;   // a member gave up waiting: the status word says so
+    auto give_up = [&]() {
+        dead = true;
+        __hip_atomic_fetch_or(a.status, kStatusTimeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    const Box box{a.xch + (size_t)g * a.members * 2 * kN};
+    auto at_box = [&](int member, uint32_t tag) { return (uint32_t)(2 * member + (int)(tag & 1)) * kBoxBytes; };
+    auto passed = [&](uint32_t tag) {   // members 0 and 1 have published `tag`
+        for (uint32_t spin = 0; !dead; ++spin) {
+            const uint64_t v = __hip_atomic_load(box.p + at_box(0, tag) / 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t u = __hip_atomic_load(box.p + at_box(1, tag) / 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((uint32_t)(v >> 32) == tag && (uint32_t)(u >> 32) == tag) break;
+            if (spin == kSpinLimit) give_up();
+            __builtin_amdgcn_s_sleep(1);
+        }
+    };
+    for (int step = a.st0; step < a.st1; ++step) {
+        const int shift = shifts(step, a.st0);
+        const uint32_t tag = (uint32_t)step + 1;
+#pragma unroll
+        for (int i = 0; i < kSlots; ++i)
+            if (i < ns) rotate<kGateT, true>(acc + team.slot(i) * kRowBytes, shift, a.offset, here(tid), y + i * kRowBytes);
+        lds_sync();
+        Cx w[2] = {}, c[kSlots][2] = {};
+        auto madd = [&](int i, const d2 (&x0)[2], Cx (&c0)[2], const d2 (&x1)[2], Cx (&c1)[2]) {
+            Cx u, v;
+            own.get(buf + i * kBufBytes, u, v);
+            mac(c0[0], u, x0[0]);
+            mac(c0[1], v, x0[1]);
+            mac(c1[0], u, x1[0]);
+            mac(c1[1], v, x1[1]);
+        };
+        for (int t = pair; t < ns * ell; t += kGateP)
+            pair_fwd_a(FromY<false>{y + (t / ell) * kRowBytes}, 24 - 8 * (t % ell), l, at, buf + t * kBufBytes, tab);
+        lds_sync();
+        for (int t = pair; t < ns * ell; t += kGateP) pair_fwd_b(l, w2, at, buf + t * kBufBytes, tab);
+        if (ns > 1) load(xe[1], ke, team.slot(1) * ell);
+        if (ns > 2) load(xe[2], ke, team.slot(2) * ell);
+        lds_sync();
+#pragma unroll
+        for (int i = 0; i < kSlots; ++i)
+            if (i < ns)
+#pragma unroll
+                for (int d = 0; d < ell; ++d) madd(i * ell + d, xe[i][d], w, xd[d], c[i]);
+        // w, and the slots without a stage-2 part
+        const int first = helper ? 0 : 1;
+        const int bt = ns < kSlots ? ns * ell : 0;
+        if (ns == kSlots) lds_sync();   // their transforms take the digits' place
+        own.put(buf + (kGateBufs - 2 + part) * kBufBytes, w);
+#pragma unroll
+        for (int i = 0; i < kSlots; ++i)
+            if (i >= first && i < ns) own.put(buf + (bt + 2 * (i - first) + part) * kBufBytes, c[i]);
+        lds_sync();
+        // tasks: w low, w high, then the slots'
+        const int ni = 2 + 2 * (ns - first);
+        auto at_inv = [&](int t) { return buf + (t < 2 ? kGateBufs - 2 + t : bt + t - 2) * kBufBytes; };
+        for (int t = pair; t < ni; t += kGateP) pair_inv_a(l, w2, at, at_inv(t), tab);
+        if (!helper) load(xf, keys(step), (1 + team.m) * ell);
+        lds_sync();
+        for (int t = pair; t < ni; t += kGateP) {
+            if (t < 2) pair_inv_b(at_inv(t), SetY{y + t * kRowBytes}, 16 * t, l, at, tab);
+            else pair_inv_b(at_inv(t), Add{acc + team.slot(first + t / 2 - 1) * kRowBytes, false}, 16 * (t & 1), l, at, tab);
+        }
+        lds_sync();
+        // this member's part of V
+        const uint32_t mine = y + 8u * tid;
+        uint32_t v0 = ldw(mine) + ldw(mine + kRowBytes), v1 = ldw(mine + 4u) + ldw(mine + kRowBytes + 4u);
+        if (helper && step > a.st0) passed(tag - 1);   // the box is free once its readers are a step on
+        box.store(at_box(team.m, tag) + 16u * tid, u4{v0, tag, v1, tag});
+        if (helper) {
+            load(xd, keys(min(step + 1, a.st1 - 1)), 0);
+            lds_sync();
+            continue;
+        }
+        {
+            u4 in[kMaxMembers - 1];
+            for (uint32_t spin = 0; !dead; ++spin) {
+                bool all = true;
+#pragma unroll
+                for (int o = 0; o < kMaxMembers - 1; ++o)
+                    if (o < members - 1) in[o] = box.load(at_box(o == 0 ? 1 - team.m : 1 + o, tag) + 16u * tid);
+#pragma unroll
+                for (int o = 0; o < kMaxMembers - 1; ++o)
+                    if (o < members - 1) all &= in[o].y == tag && in[o].w == tag;
+                if (all) break;
+                if (spin == kSpinLimit) give_up();
+            }
+#pragma unroll
+            for (int o = 0; o < kMaxMembers - 1; ++o)
+                if (o < members - 1) {
+                    v0 += in[o].x;
+                    v1 += in[o].z;
+                }
+        }
+        stw(mine, v0 + a.offset);
+        stw(mine + 4u, v1 + a.offset);
+        lds_sync();
+        if (pair < ell) pair_fwd_a(FromY<true>{y}, 24 - 8 * pair, l, at, buf + pair * kBufBytes, tab);
+        lds_sync();
+        if (pair < ell) pair_fwd_b(l, w2, at, buf + pair * kBufBytes, tab);
+        lds_sync();
+#pragma unroll
+        for (int d = 0; d < ell; ++d) {
+            Cx u, v;
+            own.get(buf + d * kBufBytes, u, v);
+            mac(c[0][0], u, xf[d][0]);
+            mac(c[0][1], v, xf[d][1]);
+        }
+        own.put(buf + (kFwd + part) * kBufBytes, c[0]);
+        lds_sync();
+        if (pair < 2) pair_inv_a(l, w2, at, buf + (kFwd + pair) * kBufBytes, tab);
+        load(xd, keys(min(step + 1, a.st1 - 1)), 0);
+        lds_sync();
+        if (pair < 2)
+            pair_inv_b(buf + (kFwd + pair) * kBufBytes, Add{acc + team.slot(0) * kRowBytes, false}, 16 * pair, l, at, tab);
+        lds_sync();
+    }
+    __syncthreads();
+    for (int j = 0; j < K1; ++j)
+        if (team.owns(j))
+            for (int i = tid; i < kN; i += kGateT) a.acc[((size_t)g * K1 + j) * kN + i] = ldw(acc + j * kRowBytes + 4u * i);
+}
+
+__global__ void fft_clear_kernel(uint64_t *p, size_t words) {
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < words) p[i] = 0;
 }
 
 }  // namespace
@@ -788,8 +1249,8 @@ static bool fft_supported(const mk_params &P) { return P.N == kN && P.bk_ell <= 
 // Automatic schedule, unless the caller forces something that only the int8
 // kernels have (GEMM tile shapes, team sizes): at N = 1024 the transforms are
 // faster at every batch size and party count (ms, int8 kernels / here: one
-// gate 34 / 9.5, 256 gates 45 / 9.5, 1024 gates 86 / 32.4 at 2 parties; 1024
-// gates 199 / 89 at 4 parties; 64 gates 180 / 61 at 8 parties).
+// gate 34 / 7.3, 256 gates 45 / 8.9, 1024 gates 86 / 31.4 at 2 parties; 1024
+// gates 199 / 89 at 4 parties; 64 gates 180 / 35 at 8 parties).
 bool use_fft(const mk_ctx *ctx) {
     const DeviceKeys &D = ctx->dev;
     return D.fft_bk && D.rot_kind == MK_ROT_AUTO && !D.team_rows && D.force_tiles[0] < 0 && D.force_tiles[1] < 0;
@@ -832,6 +1293,19 @@ int fft_upload(mk_ctx *ctx, hipStream_t s) {
         tab[kTabQ + 192 + l] = entry(8, 4 * b5 + 2);
     }
     for (int c = 0; c < 256; ++c) tab[kTab9 + c] = entry(9, c);
+    for (int q = 0; q < 4; ++q) {   // q = (j8 j7)
+        tab[kTab2 + 2 * q] = entry(3, 2 * (q >> 1));
+        tab[kTab2 + 2 * q + 1] = entry(4, 2 * q);
+    }
+    for (int w = 0; w < 2; ++w)
+        for (int l = 0; l < 64; ++l) {   // lane (j4 j3 j5 j6 j7 j0), wave j8
+            const int b4 = w * 8 + ((l >> 1) & 1) * 4 + ((l >> 2) & 1) * 2 + ((l >> 3) & 1);
+            const int q = w * 8 + ((l >> 1) & 7);
+            tab[kTab2 + kTab2Q + q] = entry(5, b4);
+            tab[kTab2 + kTab2Q + 16 + q] = entry(6, 2 * b4);
+            tab[kTab2 + kTab2R + w * 64 + l] = entry(7, 4 * b4 + 2 * (l >> 5));
+            tab[kTab2 + kTab2R + 128 + w * 64 + l] = entry(8, 8 * b4 + 4 * (l >> 5) + 2 * ((l >> 4) & 1));
+        }
     if (hipMalloc(&D.fft_tab, tab.size() * sizeof(d2)) != hipSuccess) {
         D.fft_tab = nullptr;
         return fail(MK_ENOMEM, "device allocation failed: transform tables");
@@ -848,18 +1322,39 @@ int fft_upload(mk_ctx *ctx, hipStream_t s) {
 }
 
 template <class Kernel>
-static int launch_kernel(Kernel kern, int threads, size_t lds, const FftArgs &a, hipStream_t s) {
+static int launch_kernel(Kernel kern, int blocks, int threads, size_t lds, const FftArgs &a, hipStream_t s) {
     MK_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
            "transform rotation LDS attribute");
-    hipLaunchKernelGGL(kern, dim3((unsigned)a.G), dim3(threads), lds, s, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(threads), lds, s, a);
     MK_HIP(hipGetLastError(), "transform rotation launch");
     return MK_OK;
 }
 template <int ELL>
 static int launch_ell(const FftArgs &a, bool lean, hipStream_t s) {
-    if (lean) return launch_kernel(fft_lean_kernel<ELL>, kLeanT, fft_lean_lds(a.k), a, s);
-    if (a.k > 2) return launch_kernel(fft_gate_kernel<ELL, true>, kGateT, fft_gate_lds(a.k), a, s);
-    return launch_kernel(fft_gate_kernel<ELL, false>, kGateT, fft_gate_lds(a.k), a, s);
+    if (a.members) {
+        const int blocks = a.nx * a.members * ((a.G + a.nx - 1) / a.nx);
+        return launch_kernel(fft_team_kernel<ELL>, blocks, kGateT, fft_gate_lds(a.k), a, s);
+    }
+    if (lean) return launch_kernel(fft_lean_kernel<ELL>, a.G, kLeanT, fft_lean_lds(a.k), a, s);
+    return launch_kernel(fft_gate_kernel<ELL>, a.G, kGateT, fft_gate_lds(a.k), a, s);
+}
+
+// Workgroups per gate (0: one, fft_gate_kernel or fft_lean_kernel).  As many as
+// have work and as an XCD's compute units hold for its share of the gates (a
+// workgroup takes a compute unit's LDS).  Two alone gain nothing where there is
+// work for helpers (128 gates at 2 parties 8.9 ms either way), so it takes
+// three; their box must fit the rotation's scratch, and members 0 and 1 take at
+// most two further slots each.  Measured (ms, one workgroup / team): 70 gates
+// at 2 parties 8.8 / 7.5; 64 at 4 22.3 / 15.9; 80 at 8 (teams of 3) 64 / 38.
+static int team_members(const mk_ctx *ctx, size_t count) {
+    const mk_params &P = ctx->p;
+    const DeviceKeys &D = ctx->dev;
+    if (D.num_xcd <= 0 || D.num_cus < D.num_xcd) return 0;
+    const size_t rows = (count + D.num_xcd - 1) / D.num_xcd, fit = (size_t)(D.num_cus / D.num_xcd) / rows;
+    const int useful = 2 + (P.k - 1 + kSlots - 1) / kSlots;
+    const int m = std::min((int)std::min<size_t>(fit, useful), kMaxMembers);
+    if (m < std::min(useful, 3) || P.k - 1 > kSlots * (m - 2) + 2 * (kSlots - 1)) return 0;
+    return m;
 }
 
 int launch_br_fft(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc, size_t count, int steps, hipStream_t s) {
@@ -873,20 +1368,37 @@ int launch_br_fft(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc, size_t count
     a.bk = (const d2 *)D.fft_bk; a.evk = (const d2 *)D.fft_evk; a.tab = (const d2 *)D.fft_tab;
     StageTimer t1(ctx, 1, s);
     StageTimer t4(ctx, 4, s);
-    // Which kernel: one gate per compute unit at a time, or several.  Measured
-    // on MI355X (256 compute units), fft_gate_kernel / fft_lean_kernel, ms: 2
-    // parties 256 gates 9.4 / 16.9, 512 gates 18.4 / 21.2, 1024 gates 36.8 /
-    // 32.4; 4 parties 256 gates 22.7 / 41, 512 gates 45 / 50, 1024 gates 91 /
-    // 89; 8 parties (two lean workgroups fit a compute unit) 256 gates 61 / 116,
-    // 512 gates 122 / 143.
+    // Which kernel: see team_members for several compute units per gate; one
+    // gate per compute unit at a time, or several.  Measured on MI355X (256
+    // compute units), fft_gate_kernel / fft_lean_kernel, ms: 2 parties 256 gates
+    // 8.9 / 16.9, 512 gates 17.4 / 21.2, 1024 gates 34.9 / 31.4; 4 parties 256
+    // gates 22.3 / 41, 512 gates 44.9 / 50, 1024 gates 89 / 89; 8 parties (two
+    // lean workgroups fit a compute unit) 256 gates 64 / 116, 512 gates 128 / 143.
     const size_t cus = (size_t)std::max(1, D.num_cus);
     const bool lean = P.k <= 4 && count > 2 * cus;
+    a.members = team_members(ctx, count);
+    a.nx = D.num_xcd;
+    a.status = D.status;
+    if (a.members) {
+        const size_t words = count * a.members * 2 * kN;
+        int rc = MK_OK;
+        a.xch = (uint64_t *)mfma_scratch_for(ctx, words * 8, count, s, &rc);
+        if (rc) return rc;
+        if (a.xch) {
+            hipLaunchKernelGGL(fft_clear_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, a.xch, words);
+            MK_HIP(hipGetLastError(), "transform team clear");
+            if ((rc = capture_checkpoint(ctx, s, 1))) return rc;
+        } else {
+            a.members = 0;
+        }
+    }
     // During a capture a launch ends where the stream-ordered steps (four kernels
     // each) would end a graph piece, so pieces stay as long as documented.
     for (int st = 0; st < steps || st == 0; st = std::max(a.st1, 1)) {
         const int room = capture_room(ctx);
         a.st0 = st;
         a.st1 = room == INT_MAX ? steps : std::min(steps, st + (room + 3) / 4);
+        if (a.members) a.st1 = std::min(a.st1, (st / P.n + 1) * P.n);   // a team's slots change with the party
         int rc = P.bk_ell == 3   ? launch_ell<3>(a, lean, s)
                  : P.bk_ell == 2 ? launch_ell<2>(a, lean, s)
                                  : launch_ell<1>(a, lean, s);

@@ -657,20 +657,8 @@ static Split split_for(const mk_ctx *ctx, size_t count) {
     return sp;
 }
 
-// Allocates (grows) the MFMA scratch for the parts of `sp` and fills their
-// kernel arguments (part i: gates off[i] .. off[i] + cnt[i] - 1).
-static int prepare(mk_ctx *ctx, const uint32_t *abar, const Split &sp, hipStream_t s, MfmaArgs *a) {
-    const mk_params &P = ctx->p;
-    if (P.N < 128) return fail(MK_EPARAM, "int8-MFMA path needs N >= 128");
-    const int K1 = P.k + 1, N = P.N, ell = P.bk_ell;
-    size_t need = 0;
-    for (int i = 0; i < sp.parts; ++i) {
-        const size_t GP = (sp.cnt[i] + 31) / 32 * 32;
-        // the GEMMs address a key polynomial's digit block with 32-bit offsets
-        if ((size_t)K1 * ell * GP * N >= ((size_t)1 << 31))
-            return fail(MK_EINVAL, "int8-MFMA path: batch too large for one launch (split it)");
-        need += mfma_scratch_need(P, sp.cnt[i]);
-    }
+// Makes the MFMA scratch at least `need` bytes.
+static int grow_scratch(mk_ctx *ctx, size_t need) {
     DeviceKeys &D = ctx->dev;
     if (D.mfma_scratch_bytes < need) {
         if (D.fixed_scratch) return fail(MK_EINTERNAL, "fixed scratch block too small (MFMA rotation)");
@@ -686,6 +674,41 @@ static int prepare(mk_ctx *ctx, const uint32_t *abar, const Split &sp, hipStream
         }
         D.mfma_scratch_bytes = need;
     }
+    return MK_OK;
+}
+
+// `bytes` of the MFMA scratch of a batch of `count` gates for the transform
+// rotation's teams; null where that scratch is smaller, or would have to be
+// allocated during a capture.
+void *mfma_scratch_for(mk_ctx *ctx, size_t bytes, size_t count, hipStream_t s, int *rc) {
+    DeviceKeys &D = ctx->dev;
+    const size_t need = mfma_scratch_need(ctx->p, count);
+    if (bytes > need) return nullptr;
+    if (D.mfma_scratch_bytes < bytes) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (D.fixed_scratch || hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
+            return nullptr;
+        if ((*rc = grow_scratch(ctx, need))) return nullptr;
+    }
+    return D.mfma_scratch;
+}
+
+// Allocates (grows) the MFMA scratch for the parts of `sp` and fills their
+// kernel arguments (part i: gates off[i] .. off[i] + cnt[i] - 1).
+static int prepare(mk_ctx *ctx, const uint32_t *abar, const Split &sp, hipStream_t s, MfmaArgs *a) {
+    const mk_params &P = ctx->p;
+    if (P.N < 128) return fail(MK_EPARAM, "int8-MFMA path needs N >= 128");
+    const int K1 = P.k + 1, N = P.N, ell = P.bk_ell;
+    size_t need = 0;
+    for (int i = 0; i < sp.parts; ++i) {
+        const size_t GP = (sp.cnt[i] + 31) / 32 * 32;
+        // the GEMMs address a key polynomial's digit block with 32-bit offsets
+        if ((size_t)K1 * ell * GP * N >= ((size_t)1 << 31))
+            return fail(MK_EINVAL, "int8-MFMA path: batch too large for one launch (split it)");
+        need += mfma_scratch_need(P, sp.cnt[i]);
+    }
+    DeviceKeys &D = ctx->dev;
+    if (int rc = grow_scratch(ctx, need)) return rc;
     char *sp_base = (char *)D.mfma_scratch;
     for (int i = 0; i < sp.parts; ++i) {
         const size_t GP = (sp.cnt[i] + 31) / 32 * 32;
@@ -820,8 +843,8 @@ int launch_br_mfma(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc_out, size_t 
                    hipStream_t s, uint32_t *ks_out, size_t ks_stride, bool *ks_done) {
     const mk_params &P = ctx->p;
     if (use_fft(ctx)) {
-        // one gate needs no scratch of its own; the batch limit is the same as
-        // the int8 kernels'
+        // scratch: the boxes of workgroup teams only (mfma_scratch_for); the
+        // batch limit is the same as the int8 kernels'
         const size_t GP = (count + 31) / 32 * 32;
         if ((size_t)(P.k + 1) * P.bk_ell * GP * P.N >= ((size_t)1 << 31))
             return fail(MK_EINVAL, "int8-MFMA path: batch too large for one launch (split it)");

@@ -114,3 +114,19 @@ def test_extreme_keys(torch_cuda, k, pattern):
         abar = _abar(P, cnt, cnt)
         assert np.array_equal(_rotate(torch_cuda, ctx, abar, -1, AUTO), _rotate(torch_cuda, ctx, abar, -1, STREAM)), cnt
     ctx.close()
+
+
+@pytest.mark.parametrize("k,n,cnt", [(2, 70, 3), (2, 5, 72), (2, 5, 73), (3, 5, 80), (4, 5, 81), (8, 4, 7),
+                                     (8, 4, 64), (8, 4, 73)])
+def test_teams_of_workgroups(torch_cuda, k, n, cnt):
+    """Batches narrow enough for several workgroups per gate, at the limits of
+    each team size (slots shared out to helpers and left with members 0 and
+    1) and past 64 steps of a party, twice over on one context: every word
+    equals the stream-ordered schedule's."""
+    P = _params(k, n, 3)
+    ctx = _world(P, 70 + k)
+    ctx.upload()
+    for seed in (1, 2):
+        abar = _abar(P, cnt, seed)
+        assert np.array_equal(_rotate(torch_cuda, ctx, abar, -1, AUTO), _rotate(torch_cuda, ctx, abar, -1, STREAM)), seed
+    ctx.close()
