@@ -215,6 +215,7 @@ __device__ __forceinline__ void addw(uint32_t off, uint32_t v) {
 }
 constexpr uint32_t kBufBytes = kH * 16;   // one transform
 constexpr uint32_t kRowBytes = kN * 4;    // one polynomial
+constexpr size_t kLdsBytes = 160 * 1024;  // of a compute unit
 
 // Exchanges the register pair's bit with lane bit 5 (W = 32) or 4 (W = 16).
 template <int W>
@@ -1349,7 +1350,7 @@ static int launch_ell(const FftArgs &a, bool lean, hipStream_t s) {
 static int team_members(const mk_ctx *ctx, size_t count) {
     const mk_params &P = ctx->p;
     const DeviceKeys &D = ctx->dev;
-    if (D.num_xcd <= 0 || D.num_cus < D.num_xcd) return 0;
+    if (!count || D.num_xcd <= 0 || D.num_cus < D.num_xcd) return 0;
     const size_t rows = (count + D.num_xcd - 1) / D.num_xcd, fit = (size_t)(D.num_cus / D.num_xcd) / rows;
     const int useful = 2 + (P.k - 1 + kSlots - 1) / kSlots;
     const int m = std::min((int)std::min<size_t>(fit, useful), kMaxMembers);
@@ -1357,30 +1358,16 @@ static int team_members(const mk_ctx *ctx, size_t count) {
     return m;
 }
 
-int launch_br_fft(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc, size_t count, int steps, hipStream_t s) {
-    const mk_params &P = ctx->p;
-    DeviceKeys &D = ctx->dev;
-    FftArgs a;
-    a.k = P.k; a.n = P.n; a.ell = P.bk_ell; a.G = (int)count;
-    a.st0 = 0; a.st1 = steps;
-    a.offset = decomp_offset(P.bk_ell);
-    a.abar = abar; a.acc = acc;
-    a.bk = (const d2 *)D.fft_bk; a.evk = (const d2 *)D.fft_evk; a.tab = (const d2 *)D.fft_tab;
-    StageTimer t1(ctx, 1, s);
-    StageTimer t4(ctx, 4, s);
-    // Which kernel: see team_members for several compute units per gate; one
-    // gate per compute unit at a time, or several.  Measured on MI355X (256
-    // compute units), fft_gate_kernel / fft_lean_kernel, ms: 2 parties 256 gates
-    // 8.9 / 16.9, 512 gates 17.4 / 21.2, 1024 gates 34.9 / 31.4; 4 parties 256
-    // gates 22.3 / 41, 512 gates 44.9 / 50, 1024 gates 89 / 89; 8 parties (two
-    // lean workgroups fit a compute unit) 256 gates 64 / 116, 512 gates 128 / 143.
-    const size_t cus = (size_t)std::max(1, D.num_cus);
-    const bool lean = P.k <= 4 && count > 2 * cus;
-    a.members = team_members(ctx, count);
-    a.nx = D.num_xcd;
-    a.status = D.status;
-    if (a.members) {
-        const size_t words = count * a.members * 2 * kN;
+// Gates first .. first + count - 1 of a batch on one kernel.
+static int launch_part(mk_ctx *ctx, FftArgs a, size_t first, size_t count, bool lean, int members, int steps, hipStream_t s) {
+    if (!count) return MK_OK;
+    const int n = a.n;
+    a.G = (int)count;
+    a.abar += first * ((size_t)a.k * n + 1);
+    a.acc += first * (size_t)(a.k + 1) * kN;
+    a.members = 0;
+    if (members) {
+        const size_t words = count * members * 2 * kN;
         int rc = MK_OK;
         a.xch = (uint64_t *)mfma_scratch_for(ctx, words * 8, count, s, &rc);
         if (rc) return rc;
@@ -1388,8 +1375,7 @@ int launch_br_fft(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc, size_t count
             hipLaunchKernelGGL(fft_clear_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, a.xch, words);
             MK_HIP(hipGetLastError(), "transform team clear");
             if ((rc = capture_checkpoint(ctx, s, 1))) return rc;
-        } else {
-            a.members = 0;
+            a.members = members;
         }
     }
     // During a capture a launch ends where the stream-ordered steps (four kernels
@@ -1398,14 +1384,48 @@ int launch_br_fft(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc, size_t count
         const int room = capture_room(ctx);
         a.st0 = st;
         a.st1 = room == INT_MAX ? steps : std::min(steps, st + (room + 3) / 4);
-        if (a.members) a.st1 = std::min(a.st1, (st / P.n + 1) * P.n);   // a team's slots change with the party
-        int rc = P.bk_ell == 3   ? launch_ell<3>(a, lean, s)
-                 : P.bk_ell == 2 ? launch_ell<2>(a, lean, s)
-                                 : launch_ell<1>(a, lean, s);
+        if (a.members) a.st1 = std::min(a.st1, (st / n + 1) * n);   // a team's slots change with the party
+        int rc = a.ell == 3 ? launch_ell<3>(a, lean, s) : a.ell == 2 ? launch_ell<2>(a, lean, s) : launch_ell<1>(a, lean, s);
         if (!rc) rc = capture_checkpoint(ctx, s, 4 * (a.st1 - a.st0));
         if (rc) return rc;
     }
     return MK_OK;
+}
+
+int launch_br_fft(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc, size_t count, int steps, hipStream_t s) {
+    const mk_params &P = ctx->p;
+    DeviceKeys &D = ctx->dev;
+    FftArgs a = {};
+    a.k = P.k; a.n = P.n; a.ell = P.bk_ell;
+    a.offset = decomp_offset(P.bk_ell);
+    a.abar = abar; a.acc = acc;
+    a.bk = (const d2 *)D.fft_bk; a.evk = (const d2 *)D.fft_evk; a.tab = (const d2 *)D.fft_tab;
+    a.nx = D.num_xcd; a.status = D.status;
+    StageTimer t1(ctx, 1, s);
+    StageTimer t4(ctx, 4, s);
+    // Which kernel: see team_members for several compute units per gate; one
+    // gate per compute unit at a time, or several.  Measured on MI355X (256
+    // compute units), fft_gate_kernel / fft_lean_kernel, ms: 2 parties 256 gates
+    // 8.9 / 16.9, 512 gates 17.4 / 21.2, 1024 gates 34.9 / 31.4; 4 parties 256
+    // gates 22.3 / 41, 512 gates 44.9 / 50, 768 gates 67 / 63; 8 parties (two
+    // lean workgroups fit a compute unit) 256 gates 64 / 116, 512 gates 128 / 143.
+    // What full rounds leave over runs as a batch of that size would, instead of
+    // one more round on a few compute units.  Measured, one launch / parts: 300
+    // gates at 2 parties 18.0 / 16.5, at 4 44.7 / 38.4, at 8 128 / 97.  After the
+    // lean kernel's rounds up to one gate per compute unit does from 3 parties on
+    // (800 gates at 4 parties 89 / 80, 1024 89 / 85); at 2, where its workgroups
+    // drift apart more, it does not (1100 gates 40.3 / 41.3).
+    const size_t cus = (size_t)std::max(1, D.num_cus);
+    size_t lean = P.k <= 4 && count > 2 * cus ? count : 0;
+    const size_t round = cus * std::min<size_t>(4, kLdsBytes / fft_lean_lds(P.k));
+    if (P.k > 2 && lean > round && lean % round <= cus) lean -= lean % round;
+    const size_t rest = count - lean;
+    const int members = rest ? team_members(ctx, rest % cus) : 0;
+    const size_t team = members ? rest % cus : 0;
+    int rc = launch_part(ctx, a, 0, lean, true, 0, steps, s);
+    if (!rc) rc = launch_part(ctx, a, lean, rest - team, false, 0, steps, s);
+    if (!rc) rc = launch_part(ctx, a, count - team, team, false, members, steps, s);
+    return rc;
 }
 
 }  // namespace mk

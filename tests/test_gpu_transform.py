@@ -130,3 +130,15 @@ def test_teams_of_workgroups(torch_cuda, k, n, cnt):
         abar = _abar(P, cnt, seed)
         assert np.array_equal(_rotate(torch_cuda, ctx, abar, -1, AUTO), _rotate(torch_cuda, ctx, abar, -1, STREAM)), seed
     ctx.close()
+
+
+@pytest.mark.parametrize("k,cnt", [(2, 300), (2, 1090), (4, 800), (8, 280)])
+def test_batches_in_parts(torch_cuda, k, cnt):
+    """Batches whose last gates run on another kernel than the full rounds
+    before them: every word equals the stream-ordered schedule's."""
+    P = _params(k, 3, 3)
+    ctx = _world(P, 80 + k)
+    ctx.upload()
+    abar = _abar(P, cnt, cnt)
+    assert np.array_equal(_rotate(torch_cuda, ctx, abar, -1, AUTO), _rotate(torch_cuda, ctx, abar, -1, STREAM))
+    ctx.close()
