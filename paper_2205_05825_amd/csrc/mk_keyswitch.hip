@@ -76,12 +76,18 @@ int ks_mfma_upload(mk_ctx *ctx, hipStream_t s) {
 }
 
 // Extraction and rounding, one block per (gate tile, 64 coefficients,
-// party): ks_round_unit.
+// party): ks_round_unit.  `clear`: also zeroes the party's columns of out.
 __global__ __launch_bounds__(256) void ks_round_kernel(const uint32_t *__restrict__ acc, KsShape s,
                                                        size_t count, uint32_t *__restrict__ R,
-                                                       uint32_t *__restrict__ out, size_t stride) {
+                                                       uint32_t *__restrict__ out, size_t stride, int clear) {
     __shared__ uint32_t tile[32 * 65];
     ks_round_unit<false>(acc, s, count, R, out, stride, blockIdx.x, blockIdx.y * 64, blockIdx.z, tile);
+    if (clear)
+        for (int c = blockIdx.y * 64 + threadIdx.x % 64; c < s.n; c += 64 * gridDim.y)
+            for (int gl = threadIdx.x / 64; gl < 32; gl += 4) {
+                const size_t g = (size_t)blockIdx.x * 32 + gl;
+                if (g < count) out[g * stride + 1 + (size_t)blockIdx.z * s.n + c] = 0;
+            }
 }
 
 // One ks_gemm_task per workgroup.  Tasks (party, column block, gate tile)
@@ -89,19 +95,23 @@ __global__ __launch_bounds__(256) void ks_round_kernel(const uint32_t *__restric
 // range of them: workgroup b runs on XCD b mod nx (round-robin dispatch),
 // so task = (b mod nx) per + b / nx.  A column block's key tiles (12 MB at
 // the Table 7 shape) are then fetched by at most two XCDs' L2s, instead of
-// by every XCD.
-template <bool LB2>
+// by every XCD.  SPLIT: a task is cut into `parts` ranges of `units` kKsRing
+// K-blocks each.
+template <bool LB2, bool SPLIT>
 __global__ __launch_bounds__(256, 2) void ks_gemm_kernel(const int8_t *__restrict__ tiles,
                                                          const uint32_t *__restrict__ R, KsShape s,
                                                          size_t count, uint32_t *__restrict__ out,
-                                                         size_t stride, int nx, int per) {
+                                                         size_t stride, int nx, int per, int parts, int units) {
     __shared__ __align__(16) uint4 red[kKsGemmLds / 16];
     const int GT = s.GP / 32, CB = ks_col_blocks(s);
     int task = (int)(blockIdx.x % (unsigned)nx) * per + (int)(blockIdx.x / (unsigned)nx);
-    if (task >= s.k * CB * GT) return;
+    if (task >= s.k * CB * GT * parts) return;
     const int gt = task % GT;
     task /= GT;
-    ks_gemm_task<LB2, 0>(tiles, R, s, count, out, stride, gt, task % CB, task / CB, red);
+    const int part = task % parts;
+    task /= parts;
+    const int k0 = part * units * kKsRing, k1 = min(k0 + units * kKsRing, s.N * s.KBq);
+    ks_gemm_task<LB2, 0, SPLIT>(tiles, R, s, count, out, stride, gt, task % CB, task / CB, red, k0, k1);
 }
 
 size_t ks_scratch_need(const mk_params &P, size_t count) {
@@ -164,17 +174,24 @@ int launch_ks_mfma(mk_ctx *ctx, const uint32_t *acc, uint32_t *out, size_t count
     uint32_t *R = (uint32_t *)D.ks_scratch;
     const int GT = (int)(GP / 32), CB = ks_col_blocks(sh);
     StageTimer tm(ctx, 2, s);
+    // Few gates make few tasks (12 per gate tile at the Table 7 shape), each a
+    // serial pass over 12 MB of key tiles: K is then split so that the compute
+    // units have a part each.  Measured on MI355X, whole / split: one gate 183 /
+    // 35 us (150 MB of keys at 4.3 TB/s), 33 gates 183 / 46, 201 gates 183 / 86;
+    // from half as many tasks as compute units on (352 gates) nothing is split.
+    const int whole = P.k * CB * GT, all = P.N * sh.KBq / kKsRing;
+    const int want = std::min(std::max(1, D.num_cus) / whole, all), units = want > 1 ? (all + want - 1) / want : all;
+    const int parts = (all + units - 1) / units;
     hipLaunchKernelGGL(ks_round_kernel, dim3((unsigned)GT, (unsigned)((P.N + 63) / 64), (unsigned)P.k),
-                       dim3(256), 0, s, acc, sh, count, R, out, stride);
+                       dim3(256), 0, s, acc, sh, count, R, out, stride, (int)(parts > 1));
     MK_HIP(hipGetLastError(), "key-switching round launch");
-    const int tasks = P.k * CB * GT, nx = std::max(1, D.num_xcd), per = (tasks + nx - 1) / nx;
+    const int tasks = whole * parts, nx = std::max(1, D.num_xcd), per = (tasks + nx - 1) / nx;
     const unsigned blocks = (unsigned)(nx * per);
-    if (P.ks_log_base == 2)
-        hipLaunchKernelGGL(ks_gemm_kernel<true>, dim3(blocks), dim3(256), 0, s, D.ks_win, R, sh, count, out,
-                           stride, nx, per);
-    else
-        hipLaunchKernelGGL(ks_gemm_kernel<false>, dim3(blocks), dim3(256), 0, s, D.ks_win, R, sh, count, out,
-                           stride, nx, per);
+    auto gemm = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, D.ks_win, R, sh, count, out, stride, nx, per, parts, units);
+    };
+    if (P.ks_log_base == 2) gemm(parts > 1 ? ks_gemm_kernel<true, true> : ks_gemm_kernel<true, false>);
+    else gemm(parts > 1 ? ks_gemm_kernel<false, true> : ks_gemm_kernel<false, false>);
     MK_HIP(hipGetLastError(), "key-switching GEMM launch");
     return MK_OK;
 }

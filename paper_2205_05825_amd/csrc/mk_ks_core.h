@@ -150,11 +150,13 @@ __device__ __forceinline__ ks_v4i one_hot(uint32_t r, int t, int lb, int sub, in
 // added atomically to out[g][0] (one addition per party, exact mod 2^32 in
 // any order), columns 1..n go to out[g][1 + i n + c - 1].  RAUX: cache
 // policy of the loads of R (device scope when other compute units wrote it
-// in the same launch).
-template <bool LB2, int RAUX>
+// in the same launch).  SPLIT: K-blocks k_begin .. k_end - 1 only (multiples of
+// kKsRing), every column added atomically to words that start as zero.
+template <bool LB2, int RAUX, bool SPLIT = false>
 __device__ __forceinline__ void ks_gemm_task(const int8_t *__restrict__ tiles, const uint32_t *__restrict__ R,
                                              const KsShape &s, size_t count, uint32_t *__restrict__ out,
-                                             size_t stride, int gt, int cb, int i, uint4 *red) {
+                                             size_t stride, int gt, int cb, int i, uint4 *red,
+                                             int k_begin = 0, int k_end = 0) {
     const int lane = threadIdx.x & 63, h = lane >> 5, gl = lane & 31;
     const int limb = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
     const int KB = s.N * s.KBq;
@@ -182,7 +184,8 @@ __device__ __forceinline__ void ks_gemm_task(const int8_t *__restrict__ tiles, c
     for (int m = 0; m < kKsMR; ++m) acc[m] = ks_v16i{};
     ks_v4i sa[kKsRing][kKsMR];
     uint32_t sr[kKsRing];
-    int lq = 0, lsub = 0;  // (q, sub) of the next K-block to load
+    const int k0 = SPLIT ? k_begin : 0, k1 = SPLIT ? k_end : KB;
+    int lq = k0 / s.KBq, lsub = k0 % s.KBq;  // (q, sub) of the next K-block to load
     auto advance = [&](int &q, int &sub) {
         const int wrap = sub + 1 == s.KBq;
         sub = wrap ? 0 : sub + 1;
@@ -191,13 +194,13 @@ __device__ __forceinline__ void ks_gemm_task(const int8_t *__restrict__ tiles, c
 #pragma unroll
     for (int x = 0; x < kKsRing; ++x) {
 #pragma unroll
-        for (int m = 0; m < kKsMR; ++m) sa[x][m] = ldA(m, x);
+        for (int m = 0; m < kKsMR; ++m) sa[x][m] = ldA(m, k0 + x);
         sr[x] = ldR(lq);
         advance(lq, lsub);
         __builtin_amdgcn_sched_barrier(0);
     }
-    int msub = 0;  // sub-block of the K-block being multiplied
-    for (int kb0 = 0; kb0 < KB; kb0 += kKsRing) {  // KB is a multiple of kKsRing
+    int msub = k0 % s.KBq;  // sub-block of the K-block being multiplied
+    for (int kb0 = k0; kb0 < k1; kb0 += kKsRing) {  // KB is a multiple of kKsRing
 #pragma unroll
         for (int u = 0; u < kKsRing; ++u) {
             const ks_v4i b = one_hot<LB2>(sr[u], s.t, s.lb, msub, h);
@@ -242,7 +245,10 @@ __device__ __forceinline__ void ks_gemm_task(const int8_t *__restrict__ tiles, c
             for (int e = 0; e < 4; ++e) {
                 const int c = c0 + e;
                 if (c == 0) atomicAdd(row, vals[e]);
-                else if (c <= s.n) row[(size_t)i * s.n + c] = vals[e];
+                else if (c <= s.n) {
+                    if constexpr (SPLIT) atomicAdd(row + (size_t)i * s.n + c, vals[e]);
+                    else row[(size_t)i * s.n + c] = vals[e];
+                }
             }
         }
     }

@@ -352,3 +352,23 @@ def test_autotune_picks_valid_shapes(torch_cuda):
     got = _gates_on_gpu(torch_cuda, ctx, types, c1, c2, 1)
     ref = helpers.oracle_gates("C1", types, c1, c2, idx=[0, 150, 299])
     assert np.array_equal(got[[0, 150, 299]], ref)
+
+
+@pytest.mark.parametrize("cnt", [1, 33, 201, 320, 352, 700])
+def test_keyswitch_parts(torch_cuda, cnt):
+    """Key switching with its contraction split into many, three, two and one
+    parts: the words of the int32 path, with the output's old words and its
+    padding as before."""
+    _, ctx = helpers.gpu_world("C2")
+    P = ctx.params
+    d = torch_cuda.device("cuda:0")
+    acc = np.random.default_rng(cnt).integers(0, 1 << 32, (cnt, (P.k + 1) * P.N), dtype=np.uint64).astype(np.uint32)
+    tacc = torch_cuda.from_numpy(acc.view(np.int32)).to(d)
+    outs = []
+    for path in PATHS:
+        out = torch_cuda.full((cnt, P.lwe_words + 3), 7, dtype=torch_cuda.int32, device=d)
+        ctx.extract_keyswitch(tacc, out, path=path)
+        torch_cuda.cuda.synchronize()
+        outs.append(out.cpu().numpy())
+    assert np.array_equal(outs[0], outs[1])
+    assert (outs[1][:, P.lwe_words:] == 7).all()
