@@ -1276,25 +1276,34 @@ static int launch_ell(const FftArgs &a, bool lean, hipStream_t s) {
     return launch_kernel(fft_gate_kernel<ELL>, a.G, kGateT, fft_gate_lds(a.k), a, s);
 }
 
-// Workgroups per gate (0: one, fft_gate_kernel or fft_lean_kernel).  As many as
-// have work and as an XCD's compute units hold for its share of the gates (a
-// workgroup takes a compute unit's LDS).  Two alone gain nothing where there is
-// work for helpers (128 gates at 2 parties 8.9 ms either way), so it takes
-// three; their box must fit the rotation's scratch, and members 0 and 1 take at
-// most two further slots each.  Measured (ms, one workgroup / team): 70 gates
-// at 2 parties 8.8 / 7.5; 64 at 4 22.3 / 15.9; 80 at 8 (teams of 3) 64 / 38.
+static size_t team_words(size_t count, int members) { return count * members * 2 * kN; }
+
+// Workgroups per gate (0: one, fft_gate_kernel or fft_lean_kernel): as many as
+// have work, as an XCD's compute units hold for its share of the gates (a
+// workgroup takes a compute unit's LDS), and whose boxes fit the rotation's
+// scratch.  Measured (MI355X, ms, one workgroup / team): 70 gates at 2 parties
+// 8.8 / 7.5; 64 at 4 22.3 / 15.9; 80 at 8 (teams of 3) 64 / 38.
 static int team_members(const mk_ctx *ctx, size_t count) {
     const mk_params &P = ctx->p;
     const DeviceKeys &D = ctx->dev;
     if (!count || D.num_xcd <= 0 || D.num_cus < D.num_xcd) return 0;
     const size_t rows = (count + D.num_xcd - 1) / D.num_xcd, fit = (size_t)(D.num_cus / D.num_xcd) / rows;
     const int useful = 2 + (P.k - 1 + kSlots - 1) / kSlots;
-    const int m = std::min((int)std::min<size_t>(fit, useful), kMaxMembers);
-    if (m < std::min(useful, 3) || P.k - 1 > kSlots * (m - 2) + 2 * (kSlots - 1)) return 0;
-    return m;
+    int m = std::min((int)std::min<size_t>(fit, useful), kMaxMembers);
+    while (m >= 2 && team_words(count, m) * 8 > mfma_scratch_need(P, count)) --m;
+    return m >= 2 ? m : 0;
 }
 
-// Gates first .. first + count - 1 of a batch on one kernel.
+// Whether a team of `members` runs a party's steps.  Helpers take three slots
+// each, members 0 and 1 at most two more; without helpers a team gains only
+// while there is nothing for them (128 gates at 2 parties, two members for both
+// 8.7 ms, for the first alone 8.4, one workgroup 8.7).
+static bool team_runs(int members, int party) {
+    return party <= kSlots * (members - 2) + (members > 2 ? 2 * (kSlots - 1) : 0);
+}
+
+// Gates first .. first + count - 1 of a batch on one kernel (a team's parties on
+// fft_team_kernel, the others on fft_gate_kernel).
 static int launch_part(mk_ctx *ctx, FftArgs a, size_t first, size_t count, bool lean, int members, int steps, hipStream_t s) {
     if (!count) return MK_OK;
     const int n = a.n;
@@ -1303,7 +1312,7 @@ static int launch_part(mk_ctx *ctx, FftArgs a, size_t first, size_t count, bool 
     a.acc += first * (size_t)(a.k + 1) * kN;
     a.members = 0;
     if (members) {
-        const size_t words = count * members * 2 * kN;
+        const size_t words = team_words(count, members);
         int rc = MK_OK;
         a.xch = (uint64_t *)mfma_scratch_for(ctx, words * 8, count, s, &rc);
         if (rc) return rc;
@@ -1320,6 +1329,7 @@ static int launch_part(mk_ctx *ctx, FftArgs a, size_t first, size_t count, bool 
         const int room = capture_room(ctx);
         a.st0 = st;
         a.st1 = room == INT_MAX ? steps : std::min(steps, st + (room + 3) / 4);
+        if (a.members && !team_runs(a.members, st / n)) a.members = 0;
         if (a.members) a.st1 = std::min(a.st1, (st / n + 1) * n);   // a team's slots change with the party
         int rc = a.ell == 3 ? launch_ell<3>(a, lean, s) : a.ell == 2 ? launch_ell<2>(a, lean, s) : launch_ell<1>(a, lean, s);
         if (!rc) rc = capture_checkpoint(ctx, s, 4 * (a.st1 - a.st0));
