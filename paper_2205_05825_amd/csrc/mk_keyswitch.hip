@@ -179,8 +179,13 @@ int launch_ks_mfma(mk_ctx *ctx, const uint32_t *acc, uint32_t *out, size_t count
     // units have a part each.  Measured on MI355X, whole / split: one gate 183 /
     // 35 us (150 MB of keys at 4.3 TB/s), 33 gates 183 / 46, 201 gates 183 / 86;
     // from half as many tasks as compute units on (352 gates) nothing is split.
+    // Nor where `out` lies over the accumulators (switching in place): the parts
+    // add to words that the rounding kernel clears, while its other workgroups
+    // may not have read the accumulators there.
     const int whole = P.k * CB * GT, all = P.N * sh.KBq / kKsRing;
-    const int want = std::min(std::max(1, D.num_cus) / whole, all), units = want > 1 ? (all + want - 1) / want : all;
+    const bool in_place = acc < out + count * stride && out < acc + count * (P.k + 1) * P.N;
+    const int want = in_place ? 1 : std::min(std::max(1, D.num_cus) / whole, all);
+    const int units = want > 1 ? (all + want - 1) / want : all;
     const int parts = (all + units - 1) / units;
     hipLaunchKernelGGL(ks_round_kernel, dim3((unsigned)GT, (unsigned)((P.N + 63) / 64), (unsigned)P.k),
                        dim3(256), 0, s, acc, sh, count, R, out, stride, (int)(parts > 1));

@@ -372,3 +372,21 @@ def test_keyswitch_parts(torch_cuda, cnt):
         outs.append(out.cpu().numpy())
     assert np.array_equal(outs[0], outs[1])
     assert (outs[1][:, P.lwe_words:] == 7).all()
+
+
+@pytest.mark.parametrize("name,cnt", [("C2", 1), ("C2", 33), ("C8", 5)])
+def test_keyswitch_in_place(torch_cuda, name, cnt):
+    """Key switching into the accumulators' own rows, at counts whose
+    contraction is split otherwise: the words of a switch into another buffer,
+    and the rest of each row as before."""
+    _, ctx = helpers.gpu_world(name)
+    P = ctx.params
+    acc = np.random.default_rng(cnt).integers(0, 1 << 32, (cnt, (P.k + 1) * P.N), dtype=np.uint64).astype(np.uint32)
+    tacc = torch_cuda.from_numpy(acc.view(np.int32)).to("cuda:0")
+    out = torch_cuda.zeros((cnt, P.lwe_words), dtype=torch_cuda.int32, device="cuda:0")
+    ctx.extract_keyswitch(tacc, out, path=1)
+    ctx.extract_keyswitch(tacc, tacc, path=1)
+    torch_cuda.cuda.synchronize()
+    got = tacc.cpu().numpy().view(np.uint32)
+    assert np.array_equal(got[:, :P.lwe_words], out.cpu().numpy().view(np.uint32))
+    assert np.array_equal(got[:, P.lwe_words:], acc[:, P.lwe_words:])
