@@ -842,7 +842,11 @@ static int join_parts(mk_ctx *ctx, int parts, hipStream_t s, hipStream_t *ss) {
 int launch_br_mfma(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc_out, size_t count, int steps,
                    hipStream_t s, uint32_t *ks_out, size_t ks_stride, bool *ks_done) {
     const mk_params &P = ctx->p;
-    if (use_fft(ctx)) {
+    // The int8 kernels keep the accumulators in scratch and write acc_out after
+    // the last step; the transform kernels write a gate's rows while others still
+    // read their rotation amounts, so these must lie elsewhere.
+    const bool overlap = abar < acc_out + count * (P.k + 1) * P.N && acc_out < abar + count * lwe_words(P);
+    if (use_fft(ctx) && !overlap) {
         // scratch: the boxes of workgroup teams only (mfma_scratch_for); the
         // batch limit is the same as the int8 kernels'
         const size_t GP = (count + 31) / 32 * 32;
@@ -853,7 +857,7 @@ int launch_br_mfma(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc_out, size_t 
     Split sp = split_for(ctx, count);
     // per-kernel timing and graph capture see a single stream
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (ctx->dev.profiling >= 2 || hipStreamIsCapturing(s, &cap) != hipSuccess ||
+    if (overlap || ctx->dev.profiling >= 2 || hipStreamIsCapturing(s, &cap) != hipSuccess ||
         cap != hipStreamCaptureStatusNone)
         sp = Split{1, {count, 0}, {0, 0}};
     const bool persist = use_persist(ctx, (int)((count + 31) / 32));

@@ -142,3 +142,22 @@ def test_batches_in_parts(torch_cuda, k, cnt):
     abar = _abar(P, cnt, cnt)
     assert np.array_equal(_rotate(torch_cuda, ctx, abar, -1, AUTO), _rotate(torch_cuda, ctx, abar, -1, STREAM))
     ctx.close()
+
+
+@pytest.mark.parametrize("k,cnt", [(2, 3), (2, 300), (2, 600)])
+def test_amounts_inside_the_accumulators(torch_cuda, k, cnt):
+    """Rotation amounts that lie in the buffer the accumulators are written to:
+    every word equals the rotation's with the amounts elsewhere."""
+    P = _params(k, 5, 3)
+    ctx = _world(P, 90 + k)
+    ctx.upload()
+    abar = _abar(P, cnt, cnt)
+    want = _rotate(torch_cuda, ctx, abar, -1, AUTO)
+    for at in (0, cnt * (P.k + 1) * P.N - abar.size):   # first and last words of the buffer
+        buf = torch_cuda.full((cnt, (P.k + 1) * P.N), 5, dtype=torch_cuda.int32, device="cuda:0")
+        inside = buf.view(-1)[at:at + abar.size].view(abar.shape)
+        inside.copy_(torch_cuda.from_numpy(abar.view(np.int32)))
+        ctx.blind_rotate(inside, buf)
+        torch_cuda.cuda.synchronize()
+        assert np.array_equal(buf.cpu().numpy().view(np.uint32), want), at
+    ctx.close()
