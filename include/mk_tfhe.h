@@ -409,7 +409,9 @@ int mk_get_tiles(const mk_ctx *ctx, size_t count, int32_t *gemm1_shape,
  *                      phase of a CMux step (rotate + decompose, stage 1,
  *                      stage 2).  Needs N in {128, 256, 512, 1024, 2048}.
  *   MK_ROT_AUTO        (default) at N = 1024 the transform-domain rotation:
- *                      each gate's CMux steps in one workgroup, the products
+ *                      each gate's CMux steps in one workgroup, or in a team
+ *                      of up to five where a batch (or what its full rounds
+ *                      leave over) would not fill the device, the products
  *                      through double precision transforms whose results are
  *                      proved to round to the exact integers.  With tile
  *                      shapes or a team size forced (mk_set_tiles,
@@ -445,12 +447,21 @@ int mk_set_ks_fusion(mk_ctx *ctx, int on);
 int mk_set_team_rows(mk_ctx *ctx, int rows);
 int mk_get_team_rows(const mk_ctx *ctx, size_t count, int32_t *rows);
 
+/* How long (in polls of about a microsecond; default -1: 0.2 ms) a workgroup of
+ * the transform-domain rotation waits for its team to be running before the
+ * team's gate is left to one workgroup.  Work on other streams may delay any
+ * workgroup, so a rotation never waits longer for one that has not started; 0
+ * gives every team up that is not complete at once (tests).  Results are
+ * identical either way.  Errors: MK_EINVAL. */
+int mk_set_team_wait(mk_ctx *ctx, int polls);
+
 /* Waits for `stream`, then reports and clears the context's device status
  * word, which device entry points set when they meet a condition they can
  * only detect on the GPU: MK_OK; MK_EINVAL if mk_bootstrap_gate met a gate
- * type outside NAND..XNOR since the last call; MK_EDEVICE if a persistent
- * rotation gave up waiting for another workgroup (its outputs are then
- * invalid) or ran on an XCD the upload's probe did not see.  Errors:
+ * type outside NAND..XNOR since the last call; MK_EDEVICE if a rotation (on
+ * the persistent schedule, or in teams on the transform-domain one) gave up
+ * waiting for another workgroup (its outputs are then invalid), or a
+ * persistent one ran on an XCD the upload's probe did not see.  Errors:
  * MK_EINVAL (null context), MK_ESTATE (key not uploaded), MK_EDEVICE. */
 int mk_device_status(mk_ctx *ctx, void *stream);
 

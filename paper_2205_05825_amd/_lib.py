@@ -104,6 +104,7 @@ _SIGS = {
     "mk_set_rotation": ([_vp, _i], _i),
     "mk_set_ks_fusion": ([_vp, _i], _i),
     "mk_set_team_rows": ([_vp, _i], _i),
+    "mk_set_team_wait": ([_vp, _i], _i),
     "mk_get_team_rows": ([_vp, _sz, ctypes.POINTER(ctypes.c_int32)], _i),
     "mk_device_status": ([_vp, _vp], _i),
     "mk_set_profiling": ([_vp, _i], _i),
@@ -315,9 +316,14 @@ class Context:
         _check(_L.mk_get_team_rows(self._h, int(count), ctypes.byref(r)))
         return r.value
 
+    def set_team_wait(self, polls: int = -1):
+        """How long a workgroup of the transform rotation waits for its team
+        to be running before the gate is left to one workgroup (-1: 0.2 ms)."""
+        _check(_L.mk_set_team_wait(self._h, int(polls)))
+
     def device_status(self, stream=None):
-        """Waits for the stream; raises MkError if a persistent rotation gave
-        up waiting (its outputs are then invalid)."""
+        """Waits for the stream; raises MkError if a rotation gave up waiting
+        for another workgroup (its outputs are then invalid)."""
         _check(_L.mk_device_status(self._h, _stream(stream)))
 
     # ---- profiling ----

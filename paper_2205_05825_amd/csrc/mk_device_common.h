@@ -21,7 +21,7 @@ __host__ __device__ inline uint32_t decomp_offset(int ell) {
 int hip_fail(hipError_t e, const char *what);
 
 // Bits of the context's sticky device status word (DeviceKeys::status).
-constexpr uint32_t kStatusTimeout = 1u;   // a persistent rotation gave up waiting
+constexpr uint32_t kStatusTimeout = 1u;   // a persistent or team rotation gave up waiting
 constexpr uint32_t kStatusNoXcd = 2u;     // it ran on an XCD the probe did not see
 constexpr uint32_t kStatusBadType = 4u;   // a gate type outside NAND..XNOR
 

@@ -12,7 +12,7 @@
 // (8 L + 8) ell N^2 int8 operations, and each gate's accumulator stays in LDS.
 // Three kernels: several gates per compute unit (fft_lean_kernel), one
 // (fft_gate_kernel), and several compute units per gate (fft_team_kernel, the
-// only one whose workgroups wait for each other).
+// only one whose workgroups wait for each other, and only for those that run).
 //
 // Exactness.  A key coefficient is split K = 2^16 K_hi + K_lo with signed
 // 16-bit halves; every accumulated product sum is then an integer below
@@ -569,9 +569,13 @@ struct FftArgs {
     const d2 *tab;
     // teams (fft_team_kernel)
     uint64_t *xch;          // boxes [G][members][2][N]
+    uint32_t *form;         // [G]: members that run, kApart (form_team)
     uint32_t *status;
-    int members, nx;
+    int members, nx, form_polls;
 };
+
+// Set in a gate's word: its team did not form, one workgroup runs the steps.
+constexpr uint32_t kApart = 1u << 31;
 
 // Accumulators of one gate: X^-b v, 0, .. at the start, else the rows saved before.
 template <int T>
@@ -786,6 +790,12 @@ __global__ __launch_bounds__(kGateT, 2) void fft_gate_kernel(FftArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid & 63;
     const int part = __builtin_amdgcn_readfirstlane(tid / 256);
     const int g = blockIdx.x;
+    if (a.form) {   // behind a team launch: the gates that it left
+        const uint32_t f = __builtin_amdgcn_readfirstlane(__hip_atomic_load(a.form + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        __syncthreads();
+        if (tid == 0) __hip_atomic_store(a.form + g, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!(f & kApart)) return;
+    }
     const uint32_t *abar = a.abar + (size_t)g * (a.k * a.n + 1);
     const Owner own(tid & 255, owner_word2(tid & 255), 128, a.tab);
     const int pair = wave >> 1, w2 = wave & 1;
@@ -956,12 +966,19 @@ size_t fft_gate_lds(int k) {
 // other ordering is needed.  A box has two sides by the step's parity.  Members
 // 0 and 1 publish step s only after reading step s - 1, so whoever has seen
 // their step s may overwrite the side of step s - 1 (their own words for
-// members 0 and 1, which read every step; `passed` for helpers).  Waits are
-// bounded (kSpinLimit): a member that gives up sets the status word, waits no
-// more and goes on publishing, so every workgroup ends.  A team's blocks are
-// nx apart, hence on one XCD and next to each other in its dispatch order, and
-// the team size is chosen so that all are resident at once on an idle device:
-// on a busy one a team waits until earlier work leaves room for its last member.
+// members 0 and 1, which read every step; `passed` for helpers).
+//
+// A team's blocks are nx apart, hence on one XCD and next to each other in its
+// dispatch order, and the team size is chosen so that all are resident at once
+// on an idle device.  On a busy one other streams' work can keep a member's
+// compute unit for any time, so nobody waits for a workgroup that may not run:
+// members count themselves in when they start (form_team), and one that has
+// seen its team incomplete for kFormPolls marks the gate, at which those
+// already there and those to come leave it to a launch of fft_gate_kernel that
+// follows every team launch (its other blocks end at once).  A complete team
+// holds its compute units until it ends, so its waits end too; they are bounded
+// all the same (kSpinLimit: the status word is set, the member waits no more
+// and goes on publishing).
 //
 // Bound by the latency of four transforms (2.2k cycles each), two rounds of
 // products (1.2k) and the exchange (2.2-3k, of which a load is 1.1k).  Measured
@@ -1010,6 +1027,25 @@ constexpr int kMaxMembers = 5;
 constexpr uint32_t kBoxBytes = kN * 8;   // (value, tag) words of one member and parity
 
 constexpr uint32_t kSpinLimit = 1u << 23;   // polls of about a microsecond
+// Polls before a member gives its team up: about 0.2 ms, many times what an idle
+// device takes to start a launch's workgroups, little beside a party's steps.
+constexpr int kFormPolls = 256;
+
+// One thread of each member: whether all `members` run.  The gate's word counts
+// them; kApart is set only while some are missing, so all see the same answer.
+__device__ __forceinline__ bool form_team(uint32_t *word, uint32_t members, int polls) {
+    uint32_t v = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+    for (int i = 0; v < members; ++i) {
+        if (i < polls) {
+            __builtin_amdgcn_s_sleep(1);
+            v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else if (__hip_atomic_compare_exchange_strong(word, &v, v | kApart, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT)) {
+            return false;
+        }   // else v is the word's new value: one more member or kApart
+    }
+    return v == members;
+}
 
 template <int ELL>
 __global__ __launch_bounds__(kGateT, 2) void fft_team_kernel(FftArgs a) {
@@ -1039,6 +1075,11 @@ __global__ __launch_bounds__(kGateT, 2) void fft_team_kernel(FftArgs a) {
     if (tid < kTab2Words) tab[tid] = a.tab[kTab2 + tid];
     load_acc<kGateT>(a, g, abar, acc);
     __syncthreads();
+    if (tid == 0) stw(y, form_team(a.form + g, (uint32_t)members, a.form_polls));
+    __syncthreads();
+    const bool formed = ldw(y) != 0;
+    __syncthreads();
+    if (!formed) return;
     const KeyBlock ke(a.evk, K1 * ell, word);
     d2 xd[ell][2], xe[kSlots][ell][2], xf[ell][2];
     auto load = [&](d2 (&v)[ell][2], const KeyBlock &k, int poly) {
@@ -1270,13 +1311,15 @@ template <int ELL>
 static int launch_ell(const FftArgs &a, bool lean, hipStream_t s) {
     if (a.members) {
         const int blocks = a.nx * a.members * ((a.G + a.nx - 1) / a.nx);
-        return launch_kernel(fft_team_kernel<ELL>, blocks, kGateT, fft_gate_lds(a.k), a, s);
+        if (int rc = launch_kernel(fft_team_kernel<ELL>, blocks, kGateT, fft_gate_lds(a.k), a, s)) return rc;
     }
     if (lean) return launch_kernel(fft_lean_kernel<ELL>, a.G, kLeanT, fft_lean_lds(a.k), a, s);
     return launch_kernel(fft_gate_kernel<ELL>, a.G, kGateT, fft_gate_lds(a.k), a, s);
 }
 
-static size_t team_words(size_t count, int members) { return count * members * 2 * kN; }
+static size_t box_words(size_t count, int members) { return count * members * 2 * kN; }
+// 64-bit words of a team launch's scratch: boxes, then a 32-bit word per gate.
+static size_t team_words(size_t count, int members) { return box_words(count, members) + (count + 1) / 2; }
 
 // Workgroups per gate (0: one, fft_gate_kernel or fft_lean_kernel): as many as
 // have work, as an XCD's compute units hold for its share of the gates (a
@@ -1321,6 +1364,8 @@ static int launch_part(mk_ctx *ctx, FftArgs a, size_t first, size_t count, bool 
             MK_HIP(hipGetLastError(), "transform team clear");
             if ((rc = capture_checkpoint(ctx, s, 1))) return rc;
             a.members = members;
+            a.form = (uint32_t *)(a.xch + box_words(count, members));
+            a.form_polls = ctx->dev.team_wait < 0 ? kFormPolls : ctx->dev.team_wait;
         }
     }
     // During a capture a launch ends where the stream-ordered steps (four kernels
@@ -1329,7 +1374,10 @@ static int launch_part(mk_ctx *ctx, FftArgs a, size_t first, size_t count, bool 
         const int room = capture_room(ctx);
         a.st0 = st;
         a.st1 = room == INT_MAX ? steps : std::min(steps, st + (room + 3) / 4);
-        if (a.members && !team_runs(a.members, st / n)) a.members = 0;
+        if (a.members && !team_runs(a.members, st / n)) {
+            a.members = 0;
+            a.form = nullptr;
+        }
         if (a.members) a.st1 = std::min(a.st1, (st / n + 1) * n);   // a team's slots change with the party
         int rc = a.ell == 3 ? launch_ell<3>(a, lean, s) : a.ell == 2 ? launch_ell<2>(a, lean, s) : launch_ell<1>(a, lean, s);
         if (!rc) rc = capture_checkpoint(ctx, s, 4 * (a.st1 - a.st0));
@@ -1375,3 +1423,15 @@ int launch_br_fft(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc, size_t count
 }
 
 }  // namespace mk
+
+using namespace mk;
+
+extern "C" {
+
+int mk_set_team_wait(mk_ctx *ctx, int polls) {
+    if (!ctx || polls < -1) return fail(MK_EINVAL, "mk_set_team_wait: bad argument");
+    ctx->dev.team_wait = polls;
+    return MK_OK;
+}
+
+}  // extern "C"

@@ -87,6 +87,9 @@ struct DeviceKeys {
     // Row tiles per contraction task of the persistent rotation at N = 1024
     // (mk_set_team_rows): 0 chosen by batch width, else 2, 4 or 8.
     int team_rows = 0;
+    // Polls after which a transform rotation's team that is not complete is
+    // given up (mk_set_team_wait), -1 for the default.
+    int team_wait = -1;
 };
 
 }  // namespace mk

@@ -634,7 +634,7 @@ int mk_device_status(mk_ctx *ctx, void *stream) {
     MK_HIP(hipGetLastError(), "mk_device_status: clear");
     MK_HIP(hipStreamSynchronize(s), "mk_device_status: clear sync");
     if (st & kStatusTimeout)
-        return fail(MK_EDEVICE, "persistent rotation: a workgroup timed out waiting for its team (outputs invalid)");
+        return fail(MK_EDEVICE, "blind rotation: a workgroup timed out waiting for its team (outputs invalid)");
     if (st & kStatusNoXcd) return fail(MK_EDEVICE, "persistent rotation: ran on an XCD the upload probe did not see");
     return fail(MK_EINVAL, "mk_bootstrap_gate: a gate type outside NAND..XNOR was evaluated as NAND");
 }

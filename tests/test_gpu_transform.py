@@ -13,7 +13,7 @@ from tests import helpers
 
 pytestmark = pytest.mark.gpu
 
-AUTO, STREAM = -1, 0
+AUTO, STREAM, PERSISTENT = -1, 0, 1
 
 
 @pytest.fixture(scope="module")
@@ -161,3 +161,56 @@ def test_amounts_inside_the_accumulators(torch_cuda, k, cnt):
         torch_cuda.cuda.synchronize()
         assert np.array_equal(buf.cpu().numpy().view(np.uint32), want), at
     ctx.close()
+
+
+@pytest.mark.parametrize("k,n,cnt", [(2, 5, 1), (2, 70, 73), (4, 5, 40), (8, 4, 64)])
+def test_teams_given_up(torch_cuda, k, n, cnt):
+    """A team whose members do not all run in time is left to one workgroup per
+    gate.  Waits of no, a few and the usual number of polls in turn on one
+    context: every word equals the stream-ordered schedule's, and no rotation
+    reports a time-out."""
+    P = _params(k, n, 3)
+    ctx = _world(P, 100 + k)
+    ctx.upload()
+    abar = _abar(P, cnt, cnt)
+    want = _rotate(torch_cuda, ctx, abar, -1, STREAM)
+    for polls in (0, 1, 3, -1, 0):
+        ctx.set_team_wait(polls)
+        assert np.array_equal(_rotate(torch_cuda, ctx, abar, -1, AUTO), want), polls
+        ctx.device_status()
+    ctx.close()
+
+
+@pytest.mark.parametrize("kind,rows", [(AUTO, 0), (PERSISTENT, 2)])
+def test_teams_beside_another_context(torch_cuda, kind, rows):
+    """Narrow batches on one context and stream while another context keeps
+    every compute unit busy on its own (several gates per compute unit, or
+    persistent teams of 32): both give the words they give alone."""
+    torch = torch_cuda
+    P = _params(2, 40, 3)
+    narrow, wide = _world(P, 110), _world(P, 111)
+    narrow.upload()
+    wide.upload()
+    wide.set_rotation(kind)
+    wide.set_team_rows(rows)
+    a = [torch.from_numpy(_abar(P, cnt, cnt).view(np.int32)).to("cuda:0") for cnt in (1, 64, 1500)]
+    accs = [torch.zeros((len(x), (P.k + 1) * P.N), dtype=torch.int32, device="cuda:0") for x in a]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    want = []
+    for i, x in enumerate(a):
+        (wide if i == 2 else narrow).blind_rotate(x, accs[i])
+        torch.cuda.synchronize()
+        want.append(accs[i].clone())
+        accs[i].zero_()
+    torch.cuda.synchronize()
+    for _ in range(4):
+        wide.blind_rotate(a[2], accs[2], stream=streams[1])
+        for i in (0, 1):
+            narrow.blind_rotate(a[i], accs[i], stream=streams[0])
+    torch.cuda.synchronize()
+    for i in range(3):
+        assert torch.equal(accs[i], want[i]), i
+    narrow.device_status()
+    wide.device_status()
+    narrow.close()
+    wide.close()
