@@ -76,8 +76,9 @@ int launch_ks_mfma(mk_ctx *ctx, const uint32_t *acc, uint32_t *out, size_t count
 // `count` gates (grows the rounded-coefficient scratch).
 int ks_fused_args(mk_ctx *ctx, size_t count, uint32_t *out, size_t stride, hipStream_t s, KsFused *f);
 // During a graph capture: ends the current graph after enough kernels and
-// begins the next one on the same stream (mk_engine.hip).
-int capture_checkpoint(mk_ctx *ctx, hipStream_t s, int kernels);
+// begins the next one on the same stream (mk_engine.hip).  keep_room: also
+// where the kernels that end a level would no longer fit.
+int capture_checkpoint(mk_ctx *ctx, hipStream_t s, int kernels, bool keep_room = false);
 // Kernels left in the current graph piece (INT_MAX outside a capture).
 int capture_room(const mk_ctx *ctx);
 // The whole gate pipeline on `count` gates (mk_device.hip).

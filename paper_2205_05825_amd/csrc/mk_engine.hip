@@ -476,13 +476,14 @@ struct CaptureState {
     int piece;
 };
 
-int capture_checkpoint(mk_ctx *ctx, hipStream_t s, int kernels) {
+int capture_checkpoint(mk_ctx *ctx, hipStream_t s, int kernels, bool keep_room) {
     CaptureState *cs = (CaptureState *)ctx->dev.capture;
     if (!cs) return MK_OK;
     cs->kernels += kernels;
     if (cs->kernels > kGraphMaxKernels)
         return fail(MK_EINVAL, "graph capture: a piece exceeds 4096 kernels (untested size)");
-    if (cs->kernels < cs->piece) return MK_OK;
+    const bool room = !keep_room || cs->kernels + kChunkKernels <= kGraphMaxKernels;
+    if (cs->kernels < cs->piece && room) return MK_OK;
     hipGraph_t piece = nullptr;
     if (hipStreamEndCapture(s, &piece) != hipSuccess || !piece)
         return fail(MK_EDEVICE, "graph capture: ending a piece failed");

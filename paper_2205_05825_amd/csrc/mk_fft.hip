@@ -1362,14 +1362,16 @@ static int launch_part(mk_ctx *ctx, FftArgs a, size_t first, size_t count, bool 
         if (a.xch) {
             hipLaunchKernelGGL(fft_clear_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, a.xch, words);
             MK_HIP(hipGetLastError(), "transform team clear");
-            if ((rc = capture_checkpoint(ctx, s, 1))) return rc;
             a.members = members;
             a.form = (uint32_t *)(a.xch + box_words(count, members));
             a.form_polls = ctx->dev.team_wait < 0 ? kFormPolls : ctx->dev.team_wait;
         }
     }
     // During a capture a launch ends where the stream-ordered steps (four kernels
-    // each) would end a graph piece, so pieces stay as long as documented.
+    // each, to which the few that really run are not added) would end a graph
+    // piece, so pieces stay as long as documented.  The count stays a multiple of
+    // four, so rounding the steps up takes no piece past the largest size, and
+    // keep_room leaves it the kernels that end the level.
     for (int st = 0; st < steps || st == 0; st = std::max(a.st1, 1)) {
         const int room = capture_room(ctx);
         a.st0 = st;
@@ -1380,7 +1382,7 @@ static int launch_part(mk_ctx *ctx, FftArgs a, size_t first, size_t count, bool 
         }
         if (a.members) a.st1 = std::min(a.st1, (st / n + 1) * n);   // a team's slots change with the party
         int rc = a.ell == 3 ? launch_ell<3>(a, lean, s) : a.ell == 2 ? launch_ell<2>(a, lean, s) : launch_ell<1>(a, lean, s);
-        if (!rc) rc = capture_checkpoint(ctx, s, 4 * (a.st1 - a.st0));
+        if (!rc) rc = capture_checkpoint(ctx, s, 4 * (a.st1 - a.st0), true);
         if (rc) return rc;
     }
     return MK_OK;

@@ -214,3 +214,34 @@ def test_teams_beside_another_context(torch_cuda, kind, rows):
     wide.device_status()
     narrow.close()
     wide.close()
+
+
+@pytest.mark.parametrize("n,batch", [(560, 3), (511, 140)])
+def test_largest_graph_pieces(torch_cuda, n, batch):
+    """Circuits captured in pieces of up to the largest size, at a rotation
+    longer than a piece (1120 steps count as 4480 kernels) and one that nearly
+    fills it (1022: 4088, to which the level's other kernels are added), on
+    teams and on one workgroup per gate: two replays equal the eager words."""
+    import paper_2205_05825_amd as mk
+    P = _params(2, n, 3)
+    ctx = _world(P, 120)
+    ctx.upload()
+    circ = mk.build_operator(mk.OP_ADD, 2)
+    rng = np.random.default_rng(n)
+    rows = np.stack([ctx.encrypt(i % 2, rng.integers(0, 2, batch).astype(np.uint8), seed=500 + i)
+                     for i in range(len(circ.inputs))])
+    inp = torch_cuda.from_numpy(rows.view(np.int32)).to("cuda:0")
+    want = torch_cuda.zeros((len(circ.outputs), batch, inp.shape[2]), dtype=torch_cuda.int32, device="cuda:0")
+    ctx.eval_circuit(circ, inp, want)
+    for piece in (4093, 4094, 4096):
+        out = torch_cuda.zeros_like(want)
+        ctx.set_graph_piece(piece)
+        g = ctx.circuit_graph(circ, inp, out)
+        assert g.info()[2] >= mk.circuit_stats(circ)[0] * 8 * n // 4096
+        for _ in range(2):
+            out.zero_()
+            g.launch()
+            torch_cuda.cuda.synchronize()
+            assert torch_cuda.equal(out, want), piece
+        g.close()
+    ctx.close()
