@@ -48,7 +48,9 @@ int mfma_upload(mk_ctx *ctx, const std::vector<uint32_t> &evk, hipStream_t s);
 int launch_br_mfma(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc, size_t count, int steps,
                    hipStream_t s, uint32_t *ks_out = nullptr, size_t ks_stride = 0, bool *ks_done = nullptr);
 size_t mfma_scratch_need(const mk_params &P, size_t count);
-void *mfma_scratch_for(mk_ctx *ctx, size_t bytes, size_t count, hipStream_t s, int *rc);
+size_t fft_team_scratch(const mk_ctx *ctx, size_t count);
+size_t rotation_scratch_need(const mk_ctx *ctx, size_t count);
+void *team_scratch_for(mk_ctx *ctx, size_t count, hipStream_t s, int *rc);
 // Whether a rotation of GT gate tiles runs on the persistent schedule.
 bool use_persist(const mk_ctx *ctx, int GT);
 // Gates of the first of two consecutive rotation launches for a batch of

@@ -603,7 +603,7 @@ int mk_circuit_graph_create(mk_ctx *ctx, const mk_circuit *c, const uint32_t *in
     // scratch and, on the MFMA path, the rotation's and key switch's scratch
     const size_t maxc = std::min((size_t)R.P.max_width * batch, R.chunk);
     const size_t sizes[4] = {R.wire_b + R.desc_b + R.od_b + 256, R.gate_b,
-                             path == MK_PATH_MFMA_I8 ? mfma_scratch_need(ctx->p, maxc) : 0,
+                             path == MK_PATH_MFMA_I8 ? rotation_scratch_need(ctx, maxc) : 0,
                              path == MK_PATH_MFMA_I8 ? ks_scratch_need(ctx->p, maxc) : 0};
     for (int i = 0; i < 4; ++i) {
         g->bytes[i] = sizes[i];

@@ -1321,19 +1321,28 @@ static size_t box_words(size_t count, int members) { return count * members * 2 
 // 64-bit words of a team launch's scratch: boxes, then a 32-bit word per gate.
 static size_t team_words(size_t count, int members) { return box_words(count, members) + (count + 1) / 2; }
 
+static int useful_members(const mk_params &P) { return std::min(2 + (P.k - 1 + kSlots - 1) / kSlots, kMaxMembers); }
+
+// Bytes that the teams of a rotation of up to `count` gates need: they are no
+// more workgroups than compute units.
+size_t fft_team_scratch(const mk_ctx *ctx, size_t count) {
+    const DeviceKeys &D = ctx->dev;
+    if (!D.fft_bk || D.num_xcd <= 0) return 0;
+    const size_t cus = (size_t)std::max(1, D.num_cus);
+    return box_words(1, 1) * 8 * std::min(count * useful_members(ctx->p), cus) + (std::min(count, cus) + 1) / 2 * 8;
+}
+
 // Workgroups per gate (0: one, fft_gate_kernel or fft_lean_kernel): as many as
-// have work, as an XCD's compute units hold for its share of the gates (a
-// workgroup takes a compute unit's LDS), and whose boxes fit the rotation's
-// scratch.  Measured (MI355X, ms, one workgroup / team): 70 gates at 2 parties
-// 8.8 / 7.5; 64 at 4 22.3 / 15.9; 80 at 8 (teams of 3) 64 / 38.
+// have work and as an XCD's compute units hold for its share of the gates (a
+// workgroup takes a compute unit's LDS).  Measured (MI355X, ms, one workgroup /
+// team): 70 gates at 2 parties 8.8 / 7.5; 64 at 4 22.3 / 15.9; 80 at 8 (teams
+// of 3) 64 / 38.
 static int team_members(const mk_ctx *ctx, size_t count) {
     const mk_params &P = ctx->p;
     const DeviceKeys &D = ctx->dev;
     if (!count || D.num_xcd <= 0 || D.num_cus < D.num_xcd) return 0;
     const size_t rows = (count + D.num_xcd - 1) / D.num_xcd, fit = (size_t)(D.num_cus / D.num_xcd) / rows;
-    const int useful = 2 + (P.k - 1 + kSlots - 1) / kSlots;
-    int m = std::min((int)std::min<size_t>(fit, useful), kMaxMembers);
-    while (m >= 2 && team_words(count, m) * 8 > mfma_scratch_need(P, count)) --m;
+    const int m = (int)std::min<size_t>(fit, useful_members(P));
     return m >= 2 ? m : 0;
 }
 
@@ -1357,7 +1366,7 @@ static int launch_part(mk_ctx *ctx, FftArgs a, size_t first, size_t count, bool 
     if (members) {
         const size_t words = team_words(count, members);
         int rc = MK_OK;
-        a.xch = (uint64_t *)mfma_scratch_for(ctx, words * 8, count, s, &rc);
+        a.xch = (uint64_t *)team_scratch_for(ctx, count, s, &rc);
         if (rc) return rc;
         if (a.xch) {
             hipLaunchKernelGGL(fft_clear_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, a.xch, words);

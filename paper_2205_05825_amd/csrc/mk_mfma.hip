@@ -677,18 +677,20 @@ static int grow_scratch(mk_ctx *ctx, size_t need) {
     return MK_OK;
 }
 
-// `bytes` of the MFMA scratch of a batch of `count` gates for the transform
-// rotation's teams; null where that scratch is smaller, or would have to be
-// allocated during a capture.
-void *mfma_scratch_for(mk_ctx *ctx, size_t bytes, size_t count, hipStream_t s, int *rc) {
+// Scratch of a rotation of up to `count` gates on any schedule.
+size_t rotation_scratch_need(const mk_ctx *ctx, size_t count) {
+    return std::max(mfma_scratch_need(ctx->p, count), fft_team_scratch(ctx, count));
+}
+
+// The scratch of a batch of `count` gates for the transform rotation's teams;
+// null where it would have to be allocated during a capture.
+void *team_scratch_for(mk_ctx *ctx, size_t count, hipStream_t s, int *rc) {
     DeviceKeys &D = ctx->dev;
-    const size_t need = mfma_scratch_need(ctx->p, count);
-    if (bytes > need) return nullptr;
-    if (D.mfma_scratch_bytes < bytes) {
+    if (D.mfma_scratch_bytes < fft_team_scratch(ctx, count)) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (D.fixed_scratch || hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
             return nullptr;
-        if ((*rc = grow_scratch(ctx, need))) return nullptr;
+        if ((*rc = grow_scratch(ctx, rotation_scratch_need(ctx, count)))) return nullptr;
     }
     return D.mfma_scratch;
 }
@@ -847,7 +849,7 @@ int launch_br_mfma(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc_out, size_t 
     // read their rotation amounts, so these must lie elsewhere.
     const bool overlap = abar < acc_out + count * (P.k + 1) * P.N && acc_out < abar + count * lwe_words(P);
     if (use_fft(ctx) && !overlap) {
-        // scratch: the boxes of workgroup teams only (mfma_scratch_for); the
+        // scratch: the boxes of workgroup teams only (team_scratch_for); the
         // batch limit is the same as the int8 kernels'
         const size_t GP = (count + 31) / 32 * 32;
         if ((size_t)(P.k + 1) * P.bk_ell * GP * P.N >= ((size_t)1 << 31))

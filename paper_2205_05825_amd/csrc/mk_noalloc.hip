@@ -52,7 +52,7 @@ static void noalloc_layout(const mk_ctx *ctx, size_t count, int path, size_t sz[
     const size_t abar_b = (chunk * lwe_words(P) * 4 + 255) / 256 * 256;
     sz[0] = round256(abar_b + chunk * (P.k + 1) * P.N * 4);
     const bool mfma = path == MK_PATH_MFMA_I8;
-    sz[1] = mfma ? round256(mfma_scratch_need(P, chunk)) : 0;
+    sz[1] = mfma ? round256(rotation_scratch_need(ctx, chunk)) : 0;
     sz[2] = mfma && ctx->dev.ks_win ? round256(ks_scratch_need(P, chunk)) : 0;
 }
 

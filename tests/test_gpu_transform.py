@@ -245,3 +245,41 @@ def test_largest_graph_pieces(torch_cuda, n, batch):
             assert torch_cuda.equal(out, want), piece
         g.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("k,cnt", [(1, 32), (1, 64), (2, 25), (2, 32), (2, 64), (3, 64)])
+def test_team_scratch(torch_cuda, k, cnt):
+    """Counts whose boxes need more than the int8 kernels' scratch of that
+    many gates: eagerly (twice, on scratch that grows), in the fixed block and
+    captured, every word equals the stream-ordered schedule's."""
+    import paper_2205_05825_amd as mk
+    P = _params(k, 5, 3)
+    ctx = _world(P, 130 + k)
+    ctx.upload()
+    d = "cuda:0"
+    rng = np.random.default_rng(cnt)
+    a, b = (torch_cuda.from_numpy(rng.integers(0, 1 << 32, (cnt, P.lwe_words), dtype=np.uint64).astype(np.uint32)
+                                  .view(np.int32)).to(d) for _ in range(2))
+    types = torch_cuda.full((cnt,), mk.XOR, dtype=torch_cuda.uint8, device=d)
+
+    def gates(noalloc=False):
+        out = torch_cuda.zeros_like(a)
+        ctx.bootstrap_gate(types, a, b, out, noalloc=noalloc)
+        return out
+
+    got = [gates(), gates(), gates(noalloc=True)]
+    io = torch_cuda.stack([a, b])
+    out = torch_cuda.zeros((1,) + tuple(a.shape), dtype=torch_cuda.int32, device=d)
+    g = ctx.circuit_graph(mk.Circuit(5, [2, 3], [4], np.array([[mk.XOR, 2, 3, 4]])), io, out)
+    for _ in range(2):
+        out.zero_()
+        g.launch()
+        torch_cuda.cuda.synchronize()
+        got.append(out[0].clone())
+    g.close()
+    ctx.set_rotation(STREAM)
+    want = gates()
+    torch_cuda.cuda.synchronize()
+    for i, x in enumerate(got):
+        assert torch_cuda.equal(x, want), i
+    ctx.close()
