@@ -138,7 +138,9 @@ int mk_import_keys(mk_ctx *ctx, int party, const void *buf, size_t len);
 /* The server-side "reconstruction" of the parties' keys into the evaluation
  * key (Alg. 7/8 step 1): copies the bootstrapping keys, the public keys
  * (as b_0 = -a, b_1..b_k) and the key-switching keys to the current HIP
- * device, in the layouts of both blind-rotation paths.  Synchronous on
+ * device, in the layouts of both blind-rotation paths and, at N = 1024, of the
+ * transform-domain schedule (0.66 GB at k = 8, n = 560, bk_ell = 3; where the
+ * device has no room for it, MK_ROT_AUTO runs the int8 kernels).  Synchronous on
  * `stream`.  Errors: MK_ESTATE (a party has no keys), MK_ENOMEM, MK_EDEVICE. */
 int mk_upload_eval_key(mk_ctx *ctx, void *stream);
 

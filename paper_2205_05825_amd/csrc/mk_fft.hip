@@ -1235,21 +1235,26 @@ bool use_fft(const mk_ctx *ctx) {
 }
 
 // Transforms the uploaded keys (extended form [-K | K]) and builds the twiddle
-// table; nothing for parameter sets this schedule does not run.
+// table; nothing for parameter sets this schedule does not run, nor where the
+// device has no room for them (the int8 kernels then run, as with neither).
 int fft_upload(mk_ctx *ctx, hipStream_t s) {
     const mk_params &P = ctx->p;
     DeviceKeys &D = ctx->dev;
     if (!fft_supported(P)) return MK_OK;
     const size_t bk_polys = (size_t)P.k * P.n * 3 * P.bk_ell, evk_polys = (size_t)(P.k + 1) * P.bk_ell;
-    if (hipMalloc(&D.fft_bk, bk_polys * kPoly * sizeof(d2)) != hipSuccess) {
-        D.fft_bk = nullptr;
-        return fail(MK_ENOMEM, "device allocation failed: transformed bootstrapping key");
-    }
-    if (hipMalloc(&D.fft_evk, evk_polys * kPoly * sizeof(d2)) != hipSuccess) {
-        D.fft_evk = nullptr;
-        return fail(MK_ENOMEM, "device allocation failed: transformed evaluation key");
-    }
     std::vector<d2> tab(kTabWords);
+    void **bufs[3] = {&D.fft_evk, &D.fft_tab, &D.fft_bk};
+    const size_t bytes[3] = {evk_polys * kPoly * sizeof(d2), tab.size() * sizeof(d2), bk_polys * kPoly * sizeof(d2)};
+    for (int i = 0; i < 3; ++i)
+        if (hipMalloc(bufs[i], bytes[i]) != hipSuccess) {
+            (void)hipGetLastError();   // or the next launch would report it
+            *bufs[i] = nullptr;
+            for (int j = 0; j < i; ++j) {
+                (void)hipFree(*bufs[j]);
+                *bufs[j] = nullptr;
+            }
+            return MK_OK;
+        }
     // angle of block `b` at level lv (1 .. 9): X^m = e^(i theta) splits at
     // X^(m/2) = +- e^(i theta/2)
     auto entry = [](int lv, int b) {
@@ -1284,10 +1289,6 @@ int fft_upload(mk_ctx *ctx, hipStream_t s) {
             tab[kTab2 + kTab2R + w * 64 + l] = entry(7, 4 * b4 + 2 * (l >> 5));
             tab[kTab2 + kTab2R + 128 + w * 64 + l] = entry(8, 8 * b4 + 4 * (l >> 5) + 2 * ((l >> 4) & 1));
         }
-    if (hipMalloc(&D.fft_tab, tab.size() * sizeof(d2)) != hipSuccess) {
-        D.fft_tab = nullptr;
-        return fail(MK_ENOMEM, "device allocation failed: transform tables");
-    }
     MK_HIP(hipMemcpyAsync(D.fft_tab, tab.data(), tab.size() * sizeof(d2), hipMemcpyHostToDevice, s), "transform tables");
     hipLaunchKernelGGL(fft_key_kernel, dim3((unsigned)bk_polys), dim3(256), kParts * kBufBytes, s, D.bk_ext, (const d2 *)D.fft_tab,
                        (d2 *)D.fft_bk);

@@ -283,3 +283,38 @@ def test_team_scratch(torch_cuda, k, cnt):
     for i, x in enumerate(got):
         assert torch_cuda.equal(x, want), i
     ctx.close()
+
+
+def test_upload_without_room_for_the_transforms(torch_cuda):
+    """A device whose free memory holds the int8 kernels' keys but not the
+    transformed ones (660 MB here; half of that is left): the upload succeeds,
+    the automatic schedule runs the int8 kernels, with the same words."""
+    torch = torch_cuda
+    P = _params(8, 560, 3)
+    transformed = P.k * P.n * 3 * P.bk_ell * 16384
+    abar = _abar(P, 2, 1)
+    ctx = _world(P, 140)
+    free = torch.cuda.mem_get_info()[0]
+    ctx.upload()
+    need = free - torch.cuda.mem_get_info()[0]
+    assert ctx.get_team_rows(256) == 0
+    want = _rotate(torch, ctx, abar, 600, AUTO)
+    ctx.close()
+    ctx = _world(P, 140)
+    torch.cuda.empty_cache()
+    room = torch.empty(need - transformed // 2, dtype=torch.uint8, device="cuda:0")
+    taken = []
+    for size in (8 << 30, 512 << 20, 64 << 20):     # whatever else is free
+        try:
+            while True:
+                taken.append(torch.empty(size, dtype=torch.uint8, device="cuda:0"))
+        except torch.cuda.OutOfMemoryError:
+            pass
+    del room
+    torch.cuda.empty_cache()
+    ctx.upload()
+    del taken
+    torch.cuda.empty_cache()
+    assert ctx.get_team_rows(256) > 0
+    assert np.array_equal(_rotate(torch, ctx, abar, 600, AUTO), want)
+    ctx.close()
