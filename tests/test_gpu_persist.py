@@ -200,3 +200,77 @@ def test_status_reports_bad_gate_types(torch_cuda):
     as_nand = types.copy()
     as_nand[1] = mi.NAND
     assert np.array_equal(got, helpers.oracle_gates("C1", as_nand, c1, c2))
+
+
+@pytest.mark.parametrize("rot,pairs", [(PERSISTENT, 256), (STREAM, 6)])
+def test_int8_circuits_and_graphs_table7(torch_cuda, rot, pairs):
+    """A 4-bit adder at the Table 7 shape with an int8 schedule forced:
+    persistent levels with key switching inside their launches, or four
+    kernels per step (4480 a level, cut into pieces).  Eager evaluation and
+    three replays of the captured circuit, with eager evaluations between
+    them, give the words of the automatic schedule; the sums decrypt."""
+    import paper_2205_05825_amd as mk
+    K, ctx = helpers.gpu_world("C2")
+    k = 4
+    circ = mk.build_operator(mk.OP_ADD, k)
+    a, b = mi.operand_pairs(pairs, k, seed=19)
+    in_ct = np.concatenate([helpers.encrypt_operands(K, a, k, 0, 1900), helpers.encrypt_operands(K, b, k, 1, 1910)])
+    inp = torch_cuda.from_numpy(np.ascontiguousarray(in_ct).view(np.int32)).to("cuda:0")
+    auto, out, eager = (torch_cuda.zeros((k, pairs, in_ct.shape[2]), dtype=torch_cuda.int32, device="cuda:0")
+                        for _ in range(3))
+    ctx.eval_circuit(circ, inp, auto)
+    ctx.set_rotation(rot)
+    try:
+        g = ctx.circuit_graph(circ, inp, out)
+        try:
+            for _ in range(3):
+                out.zero_()
+                eager.zero_()
+                g.launch()
+                ctx.eval_circuit(circ, inp, eager)
+                torch_cuda.cuda.synchronize()
+                ctx.device_status()
+                assert torch_cuda.equal(out, auto) and torch_cuda.equal(eager, auto)
+        finally:
+            g.close()
+    finally:
+        ctx.set_rotation(-1)
+    dec = np.stack([tfhe.decrypt(K, o) for o in auto.cpu().numpy().view(np.uint32)])
+    got = mi.from_bits(dec.T)
+    assert np.array_equal(np.asarray(got) % 16, (a + b) % 16)
+
+
+@pytest.mark.parametrize("cnt", [1100, 1280, 1344])
+def test_int8_wide_batches_in_two_launches(torch_cuda, cnt):
+    """The automatic choice among the int8 schedules at the Table 7 shape
+    (taken where GEMM tiles are forced): 1100 and 1280 gates as a full round of
+    teams and a launch of what is left, 1344 in one.  Every word equals the
+    transform schedule's."""
+    K, ctx = helpers.gpu_world("C2")
+    types, _, _, c1, c2 = _workload(K, cnt, 191)
+    assert ctx.get_team_rows(cnt) == 0
+    want = _gates(torch_cuda, ctx, types, c1, c2, -1)
+    ctx.set_tiles(0, 3)
+    try:
+        assert ctx.get_team_rows(cnt) > 0
+        got = _gates(torch_cuda, ctx, types, c1, c2, -1)
+    finally:
+        ctx.set_tiles(-1, -1)
+    assert np.array_equal(got, want)
+
+
+def test_int8_split_batches_table7(torch_cuda):
+    """300 gates at the Table 7 shape on the stream-ordered kernels, whole and
+    as two sub-batches on two streams (160 + 140), for 600 steps: the words of
+    the transform schedule."""
+    K, ctx = helpers.gpu_world("C2")
+    P = K.params
+    abar = np.random.default_rng(29).integers(0, 2 * P.N, (300, P.lwe_words)).astype(np.uint32)
+    want = _rotate(torch_cuda, ctx, abar, 600, -1)
+    for parts in (1, 2):
+        ctx.set_split(300, parts)
+        try:
+            assert ctx.get_split(300) == parts
+            assert np.array_equal(_rotate(torch_cuda, ctx, abar, 600, STREAM), want), parts
+        finally:
+            ctx.set_split(300, 0)
