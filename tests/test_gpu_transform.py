@@ -318,3 +318,17 @@ def test_upload_without_room_for_the_transforms(torch_cuda):
     assert ctx.get_team_rows(256) > 0
     assert np.array_equal(_rotate(torch, ctx, abar, 600, AUTO), want)
     ctx.close()
+
+
+@pytest.mark.parametrize("k,cnt", [(2, 1025), (3, 769), (3, 1024), (4, 1024), (8, 257)])
+def test_what_full_rounds_leave_over(torch_cuda, k, cnt):
+    """Batches just over and far over full rounds of several gates per compute
+    unit: whole on that kernel at 2 parties, the rest on one gate per compute
+    unit or on teams from 3 on.  Every word equals the stream-ordered
+    schedule's."""
+    P = _params(k, 3, 3)
+    ctx = _world(P, 150 + k)
+    ctx.upload()
+    abar = _abar(P, cnt, cnt)
+    assert np.array_equal(_rotate(torch_cuda, ctx, abar, -1, AUTO), _rotate(torch_cuda, ctx, abar, -1, STREAM))
+    ctx.close()
