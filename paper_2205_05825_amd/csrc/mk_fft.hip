@@ -779,7 +779,8 @@ constexpr int kSlots = 3;             // slots whose digits are transformed toge
 constexpr int kFwd = kSlots * kEll;   // buffers of digit transforms
 constexpr int kGateBufs = kFwd + 4;   // and of inverse transforms
 
-template <int ELL>
+// LEFT: behind a team launch, the gates that it left.
+template <int ELL, bool LEFT>
 __global__ __launch_bounds__(kGateT, 2) void fft_gate_kernel(FftArgs a) {
     constexpr int ell = ELL;
     const int K1 = a.k + 1, tid = threadIdx.x;
@@ -790,7 +791,7 @@ __global__ __launch_bounds__(kGateT, 2) void fft_gate_kernel(FftArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid & 63;
     const int part = __builtin_amdgcn_readfirstlane(tid / 256);
     const int g = blockIdx.x;
-    if (a.form) {   // behind a team launch: the gates that it left
+    if constexpr (LEFT) {
         const uint32_t f = __builtin_amdgcn_readfirstlane(__hip_atomic_load(a.form + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         __syncthreads();
         if (tid == 0) __hip_atomic_store(a.form + g, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1313,9 +1314,10 @@ static int launch_ell(const FftArgs &a, bool lean, hipStream_t s) {
     if (a.members) {
         const int blocks = a.nx * a.members * ((a.G + a.nx - 1) / a.nx);
         if (int rc = launch_kernel(fft_team_kernel<ELL>, blocks, kGateT, fft_gate_lds(a.k), a, s)) return rc;
+        return launch_kernel(fft_gate_kernel<ELL, true>, a.G, kGateT, fft_gate_lds(a.k), a, s);
     }
     if (lean) return launch_kernel(fft_lean_kernel<ELL>, a.G, kLeanT, fft_lean_lds(a.k), a, s);
-    return launch_kernel(fft_gate_kernel<ELL>, a.G, kGateT, fft_gate_lds(a.k), a, s);
+    return launch_kernel(fft_gate_kernel<ELL, false>, a.G, kGateT, fft_gate_lds(a.k), a, s);
 }
 
 static size_t box_words(size_t count, int members) { return count * members * 2 * kN; }
@@ -1386,10 +1388,7 @@ static int launch_part(mk_ctx *ctx, FftArgs a, size_t first, size_t count, bool 
         const int room = capture_room(ctx);
         a.st0 = st;
         a.st1 = room == INT_MAX ? steps : std::min(steps, st + (room + 3) / 4);
-        if (a.members && !team_runs(a.members, st / n)) {
-            a.members = 0;
-            a.form = nullptr;
-        }
+        if (a.members && !team_runs(a.members, st / n)) a.members = 0;
         if (a.members) a.st1 = std::min(a.st1, (st / n + 1) * n);   // a team's slots change with the party
         int rc = a.ell == 3 ? launch_ell<3>(a, lean, s) : a.ell == 2 ? launch_ell<2>(a, lean, s) : launch_ell<1>(a, lean, s);
         if (!rc) rc = capture_checkpoint(ctx, s, 4 * (a.st1 - a.st0), true);
