@@ -237,12 +237,11 @@ def operator_rate(torch, mk, ctx, pairs, op="add", bits=16, graph=True, sub=0, p
     sub = sub if 0 < sub < pairs else pairs
     graph = graph and sub == pairs
     w = 1
-    while w <= width:            # level batch sizes the autotuner sees first
+    while int8_rotation and w <= width:     # level batch sizes the autotuner sees first
         ctx.autotune(w * sub)
         w *= 2
     name = "%s%d" % (op, bits)
-    print("bench: %s autotuned; %s" % (name, "capturing the graph" if graph else "running"),
-          file=sys.stderr, flush=True)
+    print("bench: %s: %s" % (name, "capturing the graph" if graph else "running"), file=sys.stderr, flush=True)
     pieces = 0
     host_out = []
     if graph:
@@ -407,13 +406,19 @@ def formula_lr(torch, mk, ctx, sets, m=64, frac=8):
             "seconds": dt, "gates_per_s": sets * live / dt, "ms_per_level": dt * 1e3 / levels}
 
 
+# Whether the headline context's rotations run on the int8 kernels (--rotation,
+# --tiles), whose GEMM tiles the autotuner picks; the transform-domain rotation
+# has none.
+int8_rotation = False
+
+
 PARTY_SETS = {4: dict(C2, k=4), 8: dict(C2, k=8, bk_noise_log2=31, ks_noise_log2=16)}
 
 
 def party_scaling(torch, mk, batch, ks):
     """Table 8's party counts on the bootstrapped gate: `batch` mixed gates at
     the Table 7 shape with k parties (k = 8 with the retuned key noise), in1
-    from party 0 and in2 from party k-1, tile shapes autotuned; the second
+    from party 0 and in2 from party k-1, on the automatic schedule; the second
     of two runs is timed and every output is decrypted."""
     dev = torch.device("cuda:0")
     res = {}
@@ -429,7 +434,6 @@ def party_scaling(torch, mk, batch, ks):
         a = torch.from_numpy(c1.view(np.int32)).to(dev)
         b = torch.from_numpy(c2.view(np.int32)).to(dev)
         out = torch.zeros_like(a)
-        tiles = ctx.autotune(batch)
         for _ in range(2):
             torch.cuda.synchronize()
             t0 = time.perf_counter()
@@ -438,8 +442,7 @@ def party_scaling(torch, mk, batch, ks):
             dt = time.perf_counter() - t0
         want = np.array([mi.plain_gate(int(x), int(y), int(z)) for x, y, z in zip(types, m1, m2)])
         assert np.array_equal(ctx.decrypt(out.cpu().numpy().view(np.uint32)), want), "k=%d" % k
-        res[str(k)] = {"gates_per_s": batch / dt, "ms_per_batch": dt * 1e3, "tiles": list(tiles[:2]),
-                       "cmux_steps": k * P.n}
+        res[str(k)] = {"gates_per_s": batch / dt, "ms_per_batch": dt * 1e3, "cmux_steps": k * P.n}
         ctx.close()
         del a, b, out
         torch.cuda.empty_cache()
@@ -449,8 +452,8 @@ def party_scaling(torch, mk, batch, ks):
 
 def batch_scaling(torch, mk, ctx, sizes):
     """The headline gate mix at larger batches (wide circuit levels run at
-    these sizes): tile shapes autotuned per size, the second of two runs
-    timed, every output decrypted."""
+    these sizes): the last of three runs timed, every output decrypted; on the
+    int8 kernels with tile shapes autotuned per size."""
     dev = torch.device("cuda:0")
     res = {}
     for n in sizes:
@@ -460,8 +463,8 @@ def batch_scaling(torch, mk, ctx, sizes):
         a = torch.from_numpy(c1.view(np.int32)).to(dev)
         b = torch.from_numpy(c2.view(np.int32)).to(dev)
         out = torch.zeros_like(a)
-        tiles = ctx.autotune(n)
-        for _ in range(2):
+        tiles = ctx.autotune(n) if int8_rotation else None
+        for _ in range(3):
             torch.cuda.synchronize()
             t0 = time.perf_counter()
             ctx.bootstrap_gate(t, a, b, out)
@@ -469,9 +472,10 @@ def batch_scaling(torch, mk, ctx, sizes):
             dt = time.perf_counter() - t0
         want = np.array([mi.plain_gate(int(x), int(y), int(z)) for x, y, z in zip(types, m1, m2)])
         assert np.array_equal(ctx.decrypt(out.cpu().numpy().view(np.uint32)), want), "batch %d" % n
-        res[str(n)] = {"gates_per_s": n / dt, "ms_per_batch": dt * 1e3, "tiles": list(tiles[:2]),
-                       "persistent_team_rows": ctx.get_team_rows(n),
-                       "whole_gate_int8_tops": 8 * macs_per_gate(C2) * n / dt / 1e12}
+        res[str(n)] = {"gates_per_s": n / dt, "ms_per_batch": dt * 1e3}
+        if int8_rotation:
+            res[str(n)].update(tiles=list(tiles[:2]), persistent_team_rows=ctx.get_team_rows(n),
+                               whole_gate_int8_tops=8 * macs_per_gate(C2) * n / dt / 1e12)
     print("bench: batch sizes measured", file=sys.stderr, flush=True)
     return res
 
@@ -549,7 +553,7 @@ def main():
     ap.add_argument("--naive-pairs", type=int, default=1024,
                     help="input pairs of the scheme-vs-NAND-composed gate comparison (0: skip)")
     ap.add_argument("--tiles", default="", metavar="G1,G2",
-                    help="force the two GEMM tile shapes instead of autotuning")
+                    help="force the two GEMM tile shapes instead of autotuning (selects the int8 kernels)")
     ap.add_argument("--rotation", choices=["auto", "stream", "persistent"], default="auto",
                     help="schedule of the MFMA rotation for every run of this process (mk_set_rotation)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
@@ -598,8 +602,10 @@ def main():
 
     paths = {"mfma": mk.PATH_MFMA_I8, "i32": mk.PATH_I32}
     head = paths[args.path]
+    global int8_rotation
+    int8_rotation = args.rotation != "auto" or bool(args.tiles)
     # the autotuner times every GEMM tile shape for this batch size
-    tiles = ctx.autotune(BATCH)
+    tiles = ctx.autotune(BATCH) if int8_rotation else None
     if args.tiles:
         v1, v2 = (int(x) for x in args.tiles.split(","))
         ctx.set_tiles(v1, v2)
@@ -657,8 +663,7 @@ def main():
         roof = {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_FP64_VECTOR / 1e12,
                 "unit": "TFLOP/s fp64", "frac": achieved / PEAK_FP64_VECTOR, "traffic": None,
                 "kernel": "fft_lean_kernel", "avg_launch_ms": kms, "launches": ln[4],
-                "fp64_flops_per_launch": flops,
-                "full_hybrid_product_tops": 8 * macs / (kms * 1e-3) / 1e12}
+                "fp64_flops_per_launch": flops}
     elif persistent:
         # dominant kernel: the persistent rotation (all 1120 CMux steps of
         # the batch in one launch); executed int8 ops with live-slot
@@ -688,7 +693,7 @@ def main():
         g1_ops = 8 * (sum(2 * lv * ell for lv in live) / k) * N * N * BATCH
         g1_ms = ms[4] / max(ln[4], 1)
         achieved = g1_ops / (g1_ms * 1e-3)
-        kname = GEMM1_KERNEL[tiles[0]]
+        kname = GEMM1_KERNEL[(tiles or ctx.get_tiles(BATCH))[0]]
         traffic = measured_traffic("gemm1", kname)
         roof = {"bound": "mfma", "achieved": achieved / 1e12, "peak": PEAK_INT8_OPS / 1e12,
                 "unit": "TOP/s", "frac": achieved / PEAK_INT8_OPS, "traffic": traffic,
@@ -713,7 +718,7 @@ def main():
                                "k=2 n=560 N=1024 B=2^8 ell=3 B'=2^2 t=8",
                    "global_batch": BATCH, "path": args.path, "parallelism": "single GPU"},
         "tiles": {"gemm1_shape": tiles[0], "gemm2_shape": tiles[1], "candidate_ms": tiles[2],
-                  "sub_batches": ctx.get_split(BATCH)},
+                  "sub_batches": ctx.get_split(BATCH)} if int8_rotation else None,
         # stage times of the timed steps (HIP events around each stage, per
         # step); kernel times from one extra step with events around every
         # rotation kernel as well
@@ -745,7 +750,7 @@ def main():
     if head == mk.PATH_MFMA_I8 and args.party_gates > 0:
         res["party_scaling"] = party_scaling(torch, mk, args.party_gates, (4, 8))
         res["party_scaling"]["2"] = {"gates_per_s": value, "ms_per_batch": sec * 1e3,
-                                     "tiles": list(tiles[:2]), "cmux_steps": C2["k"] * C2["n"]}
+                                     "cmux_steps": C2["k"] * C2["n"]}
     if head == mk.PATH_MFMA_I8 and args.formula_sets > 0:
         res["lr_formula"] = formula_lr(torch, mk, ctx, args.formula_sets)
         print("bench: closed-form regression measured", file=sys.stderr, flush=True)
