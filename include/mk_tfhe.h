@@ -358,7 +358,10 @@ int mk_build_naive_gate(int type, mk_gate *gates, int32_t *n_gates, int32_t *n_w
 int mk_set_profiling(mk_ctx *ctx, int level);
 int mk_get_profile(mk_ctx *ctx, double *ms, int64_t *launches, int reset);
 
-/* Tile shapes of the int8-MFMA rotation's two GEMM kernels.  Limb-split
+/* Tile shapes of the int8-MFMA rotation's two GEMM kernels, which are those of
+ * the stream-ordered schedule: tuning, shapes and splits have no effect on the
+ * others, among them the transform-domain rotation that MK_ROT_AUTO runs at N =
+ * 1024 (mk_set_rotation); a forced shape selects the int8 kernels.  Limb-split
  * shapes, where a workgroup's four waves hold the four key limbs of one
  * output block: 0 = 256 rows x 32 gates, 1 = 128 rows x 64 gates, 2 = 128
  * rows x 32 gates, 4 = 256 rows x 64 gates; shape 3 = one wave per 64 rows
@@ -383,7 +386,7 @@ int mk_get_profile(mk_ctx *ctx, double *ms, int64_t *launches, int reset);
  *                 GEMM tails overlapping the other's GEMMs), and records
  *                 the faster batch split for this size.
  *   mk_set_tiles  forces shapes (-1 = use the tuned or default shape).
- *   mk_get_tiles  reports the shapes a batch of `count` gates would use.
+ *   mk_get_tiles  reports the shapes a batch of `count` gates would use there.
  *   mk_set_split  records the split of batches of `count` gates: 1 (whole),
  *                 2 (two sub-batches; needs count > 32) or 0 (forget).
  *   mk_get_split  reports it (1 unless tuned or set).  Splitting is skipped

@@ -16,23 +16,26 @@
 //
 // Exactness.  A key coefficient is split K = 2^16 K_hi + K_lo with signed
 // 16-bit halves; every accumulated product sum is then an integer below
-// 2^37 in magnitude, and the double result is within 0.02 of it for every
+// 2^37 in magnitude, and the double result is within 0.021 of it for every
 // input, so rounding to the nearest integer recovers it.  With u = 2^-53: a
-// butterfly's output carries a relative error (2-norm of the pair) of at
-// most 4u (table entries u each, one rounding per fused multiply-add), nine
-// levels 37u; the sum of P products of transforms 2 sqrt(2) P u.  With M = sum
-// over the P products of |u|_2 |K|_2 <= P (2^7 sqrt(N)) (2^15 sqrt(N)) = P 2^32,
-// forward errors of digits and keys reach a result coefficient through
+// forward butterfly's output carries a relative error (2-norm of the pair) of
+// at most 4u (table entries u each, one rounding per fused multiply-add), nine
+// levels 37u; an inverse one's 5u where it is scaled (subtraction, tangent,
+// multiply-add, cosine, product), else 3u, seven and two levels and the final
+// scale (4u) 45u; the sum of P products of transforms 2 sqrt(2) P u.  With M =
+// sum over the P products of |u|_2 |K|_2 <= P (2^7 sqrt(N)) (2^15 sqrt(N)) =
+// P 2^32, forward errors of digits and keys reach a result coefficient through
 // Cauchy-Schwarz as 37u M each, the products' as 2 sqrt(2) P u M, and the
-// inverse's 37u times the 2-norm of the result, at most sqrt(N) M.  For the
-// largest P, (k + 1) ell = 27 at 8 parties: 27 2^-21 (74 + 76 + 32 * 37) =
-// 0.018.  Unsplit keys would be bounded by 2^16 times as much, so the split
+// inverse's 45u times the 2-norm of the result, at most sqrt(N) M.  For the
+// largest P, (k + 1) ell = 27 at 8 parties: 27 2^-21 (74 + 76 + 32 * 45) =
+// 0.0205.  Unsplit keys would be bounded by 2^16 times as much, so the split
 // (twice the inverse transforms and products) is what makes the rounding
 // exact for every key and ciphertext and not only for likely ones.  The
 // rounding adds 1.5 2^52: the sum's low word is the integer mod 2^32.
 //
 // Butterflies are six fused multiply-adds (b (1 + i t) scaled by c, twiddle
-// c (1 + i t)).  A wave runs levels 1-8 of one transform with 8 points per
+// c (1 + i t): the cosine/tangent form of the fast Fourier transform's
+// butterflies for fused multiply-adds, Linzer and Feig 1993).  A wave runs levels 1-8 of one transform with 8 points per
 // lane: three levels in registers, two across lane bits 5 and 4
 // (v_permlane32_swap, v_permlane16_swap), one exchange through LDS, three in
 // registers.  Level 9 is done by the thread that owns the two frequencies and
@@ -1418,8 +1421,12 @@ int launch_br_fft(mk_ctx *ctx, const uint32_t *abar, uint32_t *acc, size_t count
     // one more round on a few compute units.  Measured, one launch / parts: 300
     // gates at 2 parties 18.0 / 16.5, at 4 44.7 / 38.4, at 8 128 / 97.  After the
     // lean kernel's rounds up to one gate per compute unit does from 3 parties on
-    // (800 gates at 4 parties 89 / 80, 1024 89 / 85); at 2, where its workgroups
-    // drift apart more, it does not (1100 gates 40.3 / 41.3).
+    // (1024 gates at 3 parties 56.9 / 56.1, 800 at 4 89 / 80, 1024 89 / 85); at 2,
+    // where its workgroups drift apart more, it does not (1100 gates 40.3 / 41.3).
+    // At 3 parties the lean kernel wins from 600 gates on (44.4 / 41.3; 513 gates
+    // 41.5 / 42.4); at 6 and 7 it loses at 513, 768 and 1024 gates (1024: 162 /
+    // 168, 207 / 214).  At 5 it would gain from 600 gates on (92.6 / 85.3, 1024
+    // 123 / 116 with parts) and lose at 513 (81 / 86); it is not used there.
     const size_t cus = (size_t)std::max(1, D.num_cus);
     size_t lean = P.k <= 4 && count > 2 * cus ? count : 0;
     const size_t round = cus * std::min<size_t>(4, kLdsBytes / fft_lean_lds(P.k));

@@ -597,9 +597,10 @@ static uint32_t *ctl_of(const MfmaArgs &a) {
 
 // Whether the persistent rotation runs a batch of GT gate tiles: not where the
 // automatic choice is the transform-domain rotation (use_fft), by choice
-// (mk_set_rotation), else (with forced team sizes or tiles) at N = 1024 from one tile per XCD on (the team
-// size then follows the batch width, persist_team_rows), and at other N from
-// 2.5 tiles per XCD on.  Measured on MI355X at the Table 7 shape, stream-
+// (mk_set_rotation), else at N = 1024 (with forced team sizes or tiles, or no
+// room for the transformed keys) from one tile per XCD on (the team size then
+// follows the batch width, persist_team_rows), and at other N from 2.5 tiles
+// per XCD on.  Measured on MI355X at the Table 7 shape, stream-
 // ordered against persistent (ms per batch, team size in brackets): 128
 // gates 37.8 / 49.4 (32), 256 gates 50.6 / 45.6 (32), 384 gates 66.5 / 53.0
 // (16), 512 gates 72.9 / 58.8 (16), 640 gates 81.7 / 76.6 (8), 768 gates
@@ -615,7 +616,8 @@ bool use_persist(const mk_ctx *ctx, int GT) {
 }
 
 // Gates of the first part when an automatic persistent rotation of `count`
-// gates is better run as two consecutive launches, else `count`.  At N =
+// gates (see use_persist) is better run as two consecutive launches, else
+// `count`.  At N =
 // 1024 an XCD holds U = (its compute units) / 8 teams of 8 workgroups; with
 // more than U tiles on an XCD some teams run two or more tiles phase by
 // phase.  When the tiles beyond the last full round are at most one per

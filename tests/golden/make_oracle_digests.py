@@ -1,7 +1,7 @@
 """Writes oracle_c2_digests.txt: SHA-256 digests of oracle outputs at the
 Table 7 shape (parameter set C2: k=2, n=560, N=1024, ell=3, t=8), for GPU
-parity tests that compare every output word without running the oracle on
-the GPU machine for minutes (it takes about 4 s per gate on one core).
+parity tests that compare every output word without running the oracle for
+minutes (it takes about 4 s per gate on one core).
 
 Calls only oracle/ and the plaintext workload generator mk_inputs.  Two
 records, each one digest per row over the row's uint32 words (little endian):
